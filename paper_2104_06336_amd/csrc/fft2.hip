@@ -11,6 +11,7 @@
 #include "common.h"
 #include "fft_generic.h"
 #include "fft_wave.h"
+#include "geom.h"
 #include "kernels.h"
 #include "trace.h"
 
@@ -243,10 +244,10 @@ static void launch_n(bool inv, const RowFftArgs& a, int in, int out, hipStream_t
 
 // ---------------------------------------------------------------------------------------------
 // Batched row FFTs of the lengths the wavefront FFT does not take (fft_generic.h): a workgroup
-// loads RB rows into LDS (the input modes of k_row_fft, and real rows of counts), transforms them
-// and writes them (the output modes of k_row_fft, and the row-transformed cube's transposed
-// layout), grid-stride over batches of rows, its twiddle table filled once.  Transposed outputs
-// are written rows-fastest (runs of RB consecutive rows per frequency).
+// loads RB rows into LDS (the input modes of k_row_fft), transforms them and writes them (its output
+// modes), grid-stride over batches of rows, its twiddles filled once.  Transposed outputs are written
+// rows-fastest (runs of RB consecutive rows per frequency).  RB is what LDS holds of 4096 elements,
+// less where that would leave compute units without a workgroup (1000 rows of 1000: 3 rows each).
 
 bool scan_length_ok(int n) {
   if (fast_length(n)) return true;
@@ -254,11 +255,14 @@ bool scan_length_ok(int n) {
   return n >= 16 && n % 2 == 0 && gen_plan(n, p);
 }
 
-__global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p, int inv, int in_mode, int out_mode) {
-  extern __shared__ float2 s_g[];  // twiddles [n], then rb rows of n
-  const int n = p.n, rb = gen_rows_per_block(n);
+constexpr int kGenEpt = 30;  // registers (complex) of a thread of the row passes: 4096 elements in any plan
+
+__global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p, int rb, int inv, int in_mode,
+                                                          int out_mode) {
+  extern __shared__ __align__(16) float2 s_g[];  // twiddles, then rb rows
+  const int n = p.n, stride = gen_stride(n);
   float2* tw = s_g;
-  float2* buf = s_g + n;
+  float2* buf = s_g + gen_tw_size(p);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (in_mode == IN_C64_SUM && a.stats && blockIdx.x == 0) {
     // the fused sums' per-wave counters: pair count below bit 40, 8-byte loads above
@@ -291,15 +295,15 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
     }
     if (threadIdx.x == 4 && a.ready_out) *a.ready_out = a.ready_val;
   }
-  gen_twiddles(tw, n);
-  __syncthreads();
+  gen_twiddles(tw, (double2*)buf, p);
   const int64_t nbatch = (a.nrows + rb - 1) / rb;
-  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM || out_mode == OUT_X;
+  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM;
   const int nh = n / 2 + 1;
+  const uint32_t mrb = rb == 1 ? 0u : (uint32_t)((0x100000000ull + rb - 1) / rb);
   for (int64_t bt = blockIdx.x; bt < nbatch; bt += gridDim.x) {
     const int64_t r0 = bt * rb;
-    for (int e = threadIdx.x; e < rb * n; e += blockDim.x) {
-      const int rl = e / n, i = e % n;
+    for (int e = threadIdx.x; e < rb * n; e += kGenThreads) {
+      const int rl = gdiv(e, p.mn), i = e - rl * n;
       const int64_t r = r0 + rl;
       float2 x = make_float2(0.f, 0.f);
       if (r < a.nrows) {
@@ -325,36 +329,33 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
         } else if (in_mode == IN_F32_PAIR) {
           x.x = a.in_f0[el] * a.s0;
           x.y = a.in_f1 ? a.in_f1[el] * a.s1 : 0.f;
-        } else if (in_mode == IN_F64_PAIR) {
+        } else {
           x.x = (float)(a.in_d0[el] * (double)a.s0);
           x.y = a.in_d1 ? (float)(a.in_d1[el] * (double)a.s1) : 0.f;
-        } else if (in_mode == IN_U8) {
-          x.x = (float)((const uint8_t*)a.in_u)[el];
-        } else {
-          x.x = (float)((const uint16_t*)a.in_u)[el];
         }
       }
-      buf[e] = inv ? cconj(x) : x;
+      buf[rl * stride + gpad(i)] = inv ? cconj(x) : x;
     }
     __syncthreads();
-    gen_fft(buf, tw, p, rb);
-    for (int e = threadIdx.x; e < rb * n; e += blockDim.x) {
+    gen_pass<kGenEpt, kGenThreads, false>(buf, stride, tw, p.p[0], rb);
+    for (int s = 1; s < p.np; ++s) {
+      const GPass ps = p.p[s];
+      gen_pass<kGenEpt, kGenThreads, true>(buf, stride, tw, ps, rb);
+    }
+    for (int e = threadIdx.x; e < rb * n; e += kGenThreads) {
       // transposed outputs rows-fastest, the others along the row
-      const int rl = transposed ? e % rb : e / n, m = transposed ? e / rb : e % n;
+      const int hi = transposed ? gdiv(e, mrb) : gdiv(e, p.mn);
+      const int rl = transposed ? e - hi * rb : hi, m = transposed ? hi : e - hi * n;
       const int64_t r = r0 + rl;
       if (r >= a.nrows) continue;
-      const float2 y = buf[rl * n + m];
+      const float2 y = buf[rl * stride + gpad(m)];
       const float2 v = cmul(inv ? cconj(y) : y, a.osc);
       if (out_mode == OUT_ROW_C64) a.out_c[r * n + m] = v;
       else if (out_mode == OUT_ROW_RE) a.out_f[r * n + m] = v.x;
       else if (out_mode == OUT_ROW_IM) a.out_f[r * n + m] = v.y;
       else if (out_mode == OUT_T_C64) a.out_c[(int64_t)m * a.out_stride + r] = v;
       else if (out_mode == OUT_T_RE) a.out_f[(int64_t)m * a.out_stride + r] = v.x;
-      else if (out_mode == OUT_T_IM) a.out_f[(int64_t)m * a.out_stride + r] = v.y;
-      else if (m < nh) {
-        const int64_t kd = r / a.xrows, y_ = r % a.xrows;
-        a.out_c[(kd * nh + m) * a.xrows + y_] = v;
-      }
+      else a.out_f[(int64_t)m * a.out_stride + r] = v.y;
     }
     __syncthreads();
   }
@@ -363,13 +364,109 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
 static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream) {
   GPlan p;
   if (!gen_plan(n, p)) return STEM_EINVAL;
-  const int rb = gen_rows_per_block(n);
+  int64_t rb = kGenMax / n;
+  if (rb > gen_max_rows(p, kGenThreads, kGenEpt)) rb = gen_max_rows(p, kGenThreads, kGenEpt);
+  if (rb > a.nrows / 256) rb = a.nrows / 256;
+  if (rb < 1) rb = 1;
   const int64_t batches = (a.nrows + rb - 1) / rb;
-  const size_t lds = (size_t)(n + rb * n) * sizeof(float2);
+  const size_t lds = gen_lds(p, (int)rb, gen_stride(n));
   const int res = resident_blocks((const void*)k_grow_fft, kGenThreads, lds);
   const int64_t cap = res > 0 ? res : 1024;
   hipLaunchKernelGGL(k_grow_fft, dim3((unsigned)(batches < cap ? batches : cap)), dim3(kGenThreads), lds, stream, a,
-                     p, inverse ? 1 : 0, (int)in, (int)out);
+                     p, (int)rb, inverse ? 1 : 0, (int)in, (int)out);
+  STEM_LAUNCH_CHECK();
+  return STEM_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Row transform of the binned counts at any length: real rows r = kd ny + y of n counts, X[kd][m][y] for
+// m <= n/2.  Two real rows make one complex transform; the workgroup splits the 2 RB half spectra from
+// LDS and writes them in runs of 2 RB consecutive y (16-byte pairs: ny is even, so a pair is of one
+// pixel).  The first pass reads the counts straight from global memory (neighbouring threads,
+// neighbouring counts).  Workgroups of 512 threads with up to 64 KB of rows, two per compute unit;
+// RB is a power of two, so that a thread keeps its row pair through the write loop.
+//
+// Bound by LDS traffic and the writes of X.  Measured (one MI355X): 1000 x 1000 scan, 176 pixels of
+// 8-bit counts, 473 us against 1640 us for one real row per complex transform written in runs of four;
+// 96 x 160, 793 pixels of 16-bit counts, 25 us against 159 us.
+constexpr int kGenXThreads = 512;
+constexpr int kGenXEpt = 24;
+
+template <typename DT>
+__global__ void __launch_bounds__(kGenXThreads, 4) k_grow_x(const DT* __restrict__ D, GPlan p, int lrb, int stride,
+                                                            int ny, uint32_t nrows, Magic mny,
+                                                            float2* __restrict__ X) {
+  extern __shared__ __align__(16) float2 s_g[];  // twiddles, then rb rows
+  const int n = p.n, nh = n / 2 + 1, rb = 1 << lrb;
+  float2* tw = s_g;
+  float2* buf = s_g + gen_tw_size(p);
+  gen_twiddles(tw, (double2*)buf, p);
+  const uint32_t tr = 2u << lrb, ntiles = (nrows + tr - 1) / tr;
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t r0 = tile * tr;
+    gen_radix(p.p[0].r, [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      const int tid = gen_tid();
+      float2 v[R * gen_per_thread(R, kGenXEpt)];
+      gen_each<R, kGenXEpt, kGenXThreads>(tid, p.p[0], rb, [&](int b, int row, int j) {
+        const uint32_t r = r0 + 2 * row;  // nrows is even
+        const DT* src = D + (int64_t)r * n + j;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          float2 x = make_float2(0.f, 0.f);
+          if (r < nrows) x = make_float2((float)src[q * p.p[0].m], (float)src[n + q * p.p[0].m]);
+          v[b * R + q] = x;
+        }
+      });
+      gen_compute<R, kGenXEpt, kGenXThreads, false>(tid, v, tw, p.p[0], rb);
+      gen_write<R, kGenXEpt, kGenXThreads>(tid, v, buf, stride, p.p[0], rb);
+    });
+    __syncthreads();
+    for (int s = 1; s < p.np; ++s) gen_pass<kGenXEpt, kGenXThreads, true>(buf, stride, tw, p.p[s], rb);
+    // z = a + i b of rows (2p, 2p+1): A(m) = (z(m) + conj z(-m))/2, B(m) = (z(m) - conj z(-m))/(2i)
+    const int pr = (int)threadIdx.x & (rb - 1);
+    const uint32_t r = r0 + 2 * pr;
+    if (r < nrows) {
+      const uint32_t kd = magic_div(r, mny), ry = r - kd * ny;
+      float2* out = X + (int64_t)kd * nh * ny + ry;
+      const float2* z = buf + pr * stride;
+      for (int m = (int)threadIdx.x >> lrb; m < nh; m += kGenXThreads >> lrb) {
+        const float2 u = z[gpad(m)], w = cconj(z[gpad(m ? n - m : 0)]);
+        const float2 va = cscale(cadd(u, w), 0.5f), vb = cscale(cmul_mi(csub(u, w)), 0.5f);
+        *(float4*)(out + (int64_t)m * ny) = make_float4(va.x, va.y, vb.x, vb.y);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2* X, hipStream_t stream) {
+  GPlan p;
+  if (!gen_plan(n, p) || (ny & 1) || (nrows & 1) || nrows <= 0 || nrows >= (1ll << 31)) return STEM_EINVAL;
+  STEM_TRACE("xstage_fft", stream);
+  // row pairs per workgroup: 64 KB of rows at most; past 8 (runs of 128 bytes) only while every
+  // compute unit still gets two workgroups
+  const int most = gen_max_rows(p, kGenXThreads, kGenXEpt);
+  int lrb = 0;
+  while ((2 << lrb) <= most && (2 << lrb) * gen_stride(n) <= 8704 &&
+         ((2 << lrb) <= 8 || nrows >= (4ll << lrb) * 512))
+    ++lrb;
+  // the row stride: 1 / rb of the banks apart modulo the 32 of 8 bytes, so that the rb rows of one
+  // frequency, read together by the split, lie in different banks
+  int stride = gen_stride(n);
+  const int step = 32 >> lrb ? 32 >> lrb : 1;
+  while (lrb && (stride & 31) != step) ++stride;
+  const size_t lds = gen_lds(p, 1 << lrb, stride);
+  auto go = [&](auto dt) {
+    using DT = decltype(dt);
+    const int64_t tiles = (nrows + (2 << lrb) - 1) / (2 << lrb);
+    const int res = resident_blocks((const void*)k_grow_x<DT>, kGenXThreads, lds);
+    const int64_t cap = res > 0 ? res : 512;
+    hipLaunchKernelGGL(k_grow_x<DT>, dim3((unsigned)(tiles < cap ? tiles : cap)), dim3(kGenXThreads), lds, stream,
+                       (const DT*)D, p, lrb, stride, ny, (uint32_t)nrows, make_magic((uint32_t)ny), X);
+  };
+  if (d_bits == 8) go(uint8_t{});
+  else go(uint16_t{});
   STEM_LAUNCH_CHECK();
   return STEM_OK;
 }
@@ -377,7 +474,7 @@ static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFf
 int launch_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream) {
   if (a.nrows <= 0) return STEM_OK;
   STEM_TRACE(a.tag ? a.tag : "row_fft", stream);
-  if (!fast_length(n) || in == IN_U8 || in == IN_U16 || out == OUT_X) return launch_generic(n, inverse, in, out, a, stream);
+  if (!fast_length(n)) return launch_generic(n, inverse, in, out, a, stream);
   switch (n) {
     case 32: launch_n<32>(inverse, a, in, out, stream); break;
     case 64: launch_n<64>(inverse, a, in, out, stream); break;

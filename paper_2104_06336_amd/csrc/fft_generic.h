@@ -1,70 +1,156 @@
-// Mixed-radix FFT of any length N = 2^a 3^b 5^c up to kGenMax, for the scan sizes the wavefront FFT
-// of fft_wave.h does not take (not a power of two, or longer than 1024).
+// Mixed-radix FFT of any even length N = 2^a 3^b 5^c up to kGenMax, for the scan sizes the wavefront
+// FFT of fft_wave.h does not take (not a power of two, or longer than 1024).
 //
-// A workgroup transforms RB = max(1, 4096/N) rows at once in LDS with a Stockham autosort FFT:
-// pass s of radix R, with Ns the product of the earlier radices, takes butterfly j (0 <= j < N/R)
-// from elements j + q N/R (q < R), multiplies element q by w^(q (j mod Ns)) with w =
-// exp(-2 pi i / (Ns R)), applies the length-R DFT and writes element q to
-// (j div Ns) Ns R + (j mod Ns) + q Ns.  Every thread reads all its butterflies' inputs before the
-// workgroup barrier and writes after it, so one LDS buffer serves each pass in place.  Twiddles
-// come from an LDS table of W_N^t = exp(-2 pi i t/N), t < N, evaluated in FP64 with the angle
-// 2t/N (an exact integer ratio) and rounded to FP32; the exponent q (j mod Ns) N/(Ns R) is an
-// integer below N.  Radices are taken as 4 while 4 divides what is left, then 2, 3, 5.
+// A workgroup transforms RB rows at once in LDS with a Stockham autosort FFT: pass s of radix R, with
+// Ns the product of the earlier radices and m = N/R, takes butterfly j (0 <= j < m) from elements
+// j + q m (q < R), multiplies element q by w^(q (j mod Ns)) with w = exp(-2 pi i / (Ns R)), applies the
+// length-R DFT and writes element q to (j div Ns) Ns R + (j mod Ns) + q Ns.  Every thread reads all
+// its butterflies' inputs before the workgroup barrier and writes after it, so one LDS buffer serves
+// each pass in place.
+//
+// What bounds it is LDS traffic, index arithmetic and barriers, all per pass, so the plan takes the
+// fewest passes it can: radices up to 16 (1000 = 10.10.10, 96 = 6.16, 2000 = 5.5.8.10), the composite
+// ones in registers (products of coprime lengths by the prime-factor map, without twiddles).  The
+// twiddles lie in LDS per pass in the order the butterflies read them ([q - 1][j mod Ns], N - R0
+// entries in all), the quotients by m and Ns are multiply-high by constants of the plan.  Against radices
+// 4, 2, 3, 5 taken one by one with a table of W_N^t (an FP64 sincospi per entry and workgroup) and
+// integer divisions, 1000 rows of 1000 take 23 us instead of 30 us (one MI355X), 160 rows of 96 6.7 us
+// instead of 23 us.
 #pragma once
 
 #include "common.h"
+#include "fft_wave.h"
 
 namespace stem {
 
 constexpr int kGenMax = 4096;     // longest transform
-constexpr int kGenThreads = 256;  // threads of a generic-FFT workgroup
-constexpr int kGenMaxPasses = 12;
+constexpr int kGenThreads = 256;  // threads of a generic-FFT workgroup of the row passes
+constexpr int kGenMaxPasses = 6;
+
+// One pass: radix r, m = n/r, ns the product of the earlier radices, off the pass's first twiddle,
+// step = n/(ns r); mm and mns divide by m and ns (gdiv).
+struct GPass {
+  int32_t r, m, ns, off, step;
+  uint32_t mm, mns;
+};
 
 struct GPlan {
   int32_t n;
   int32_t np;
-  int32_t r[kGenMaxPasses];
+  int32_t ntw;  // twiddles of the passes after the first: n - r0
+  uint32_t mn;  // divides by n
+  GPass p[kGenMaxPasses];
 };
 
-// N = 2^a 3^b 5^c with 2 <= N <= kGenMax, factored into passes; false otherwise.
-inline bool gen_plan(int n, GPlan& p) {
-  if (n < 2 || n > kGenMax) return false;
-  p.n = n;
-  p.np = 0;
-  int m = n;
-  while (m % 4 == 0 && p.np < kGenMaxPasses) { p.r[p.np++] = 4; m /= 4; }
-  while (m % 2 == 0 && p.np < kGenMaxPasses) { p.r[p.np++] = 2; m /= 2; }
-  while (m % 3 == 0 && p.np < kGenMaxPasses) { p.r[p.np++] = 3; m /= 3; }
-  while (m % 5 == 0 && p.np < kGenMaxPasses) { p.r[p.np++] = 5; m /= 5; }
-  return m == 1;
-}
+// x / d for 0 <= x < 2^17, 1 <= d <= 4096: with mag = ceil(2^32 / d), mag d - 2^32 < d and x d < 2^29,
+// so the error x (mag d - 2^32) / (d 2^32) stays below 1/d.  d = 1 has no 32-bit mag (0 stands for it).
+inline uint32_t gmagic(int d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
+__device__ __forceinline__ int gdiv(int x, uint32_t mag) { return mag ? (int)__umulhi((uint32_t)x, mag) : x; }
 
-__host__ __device__ inline int gen_rows_per_block(int n) { return n >= kGenMax ? 1 : kGenMax / n; }
+constexpr int kGenRadices[11] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16};
 
-// tw[t] = exp(-2 pi i t / n), t < n (FP64 evaluation, FP32 rounding); every thread of the workgroup
-// takes part
-__device__ __forceinline__ void gen_twiddles(float2* tw, int n) {
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
-    double s, c;
-    sincospi(2.0 * (double)t / (double)n, &s, &c);
-    tw[t] = make_float2((float)c, (float)-s);
+// The radices of n, ascending, as few as possible and then with the smallest sum (balanced); false
+// when n is no product of them.
+inline bool gen_factor(int n, int from, int depth, int* cur, int* best, int& best_np, int& best_sum) {
+  if (n == 1) {
+    int sum = 0;
+    for (int i = 0; i < depth; ++i) sum += cur[i];
+    if (depth >= 2 && (depth < best_np || (depth == best_np && sum < best_sum))) {
+      best_np = depth;
+      best_sum = sum;
+      for (int i = 0; i < depth; ++i) best[i] = cur[i];
+    }
+    return true;
   }
+  if (depth >= kGenMaxPasses || depth >= best_np) return false;
+  for (int i = from; i < 11; ++i) {
+    const int r = kGenRadices[i];
+    if (r > n) break;
+    if (n % r) continue;
+    cur[depth] = r;
+    gen_factor(n / r, i, depth + 1, cur, best, best_np, best_sum);
+  }
+  return best_np <= kGenMaxPasses;
 }
 
+// The plan of n = 2^a 3^b 5^c, 4 <= n <= kGenMax (at least two passes); false otherwise.  The largest
+// radix is the last pass's: its butterflies are the fewest, at most one per thread in the fused sum.
+inline bool gen_plan(int n, GPlan& p) {
+  if (n < 4 || n > kGenMax) return false;
+  int cur[kGenMaxPasses], best[kGenMaxPasses], np = kGenMaxPasses + 1, sum = 0;
+  gen_factor(n, 0, 0, cur, best, np, sum);
+  if (np > kGenMaxPasses) return false;
+  p.n = n;
+  p.np = np;
+  p.ntw = n - best[0];
+  p.mn = gmagic(n);
+  int ns = 1;
+  for (int s = 0; s < np; ++s) {
+    GPass& q = p.p[s];
+    q.r = best[s];
+    q.m = n / q.r;
+    q.ns = ns;
+    q.off = s ? ns - best[0] : 0;  // passes 1 .. s-1 hold ns (r - 1) entries each
+    q.step = n / (ns * q.r);
+    q.mm = gmagic(q.m);
+    q.mns = gmagic(q.ns);
+    ns *= q.r;
+  }
+  return true;
+}
+
+// Butterflies of radix r a thread takes in a pass with ept registers, and the rows of a workgroup of
+// t threads that respect it in every pass.
+__host__ __device__ constexpr int gen_per_thread(int r, int ept) { return ept / r > 1 ? ept / r : 1; }
+inline int gen_max_rows(const GPlan& p, int threads, int ept) {
+  int rb = kGenMax;
+  for (int s = 0; s < p.np; ++s) {
+    const int k = threads * gen_per_thread(p.p[s].r, ept) / p.p[s].m;
+    rb = k < rb ? k : rb;
+  }
+  return rb;
+}
+
+// LDS position of element i of a row (one element of padding per 16: the strides Ns of the passes'
+// writes are often multiples of 8 or 16) and the row stride.
+__host__ __device__ __forceinline__ int gpad(int i) { return i + (i >> 4); }
+__host__ __device__ inline int gen_stride(int n) { return gpad(n - 1) + 1; }
+
+// LDS of a workgroup in float2: the twiddles (an even number of entries, so that what follows is
+// 16-byte aligned), then the rows (at least the 128 double2 that gen_twiddles works in)
+__host__ __device__ inline int gen_tw_size(const GPlan& p) { return (p.ntw + 1) & ~1; }
+inline size_t gen_lds(const GPlan& p, int rows, int stride) {
+  const size_t b = (size_t)rows * stride;
+  return ((size_t)gen_tw_size(p) + (b < 256 ? 256 : b)) * sizeof(float2);
+}
+
+// The passes' twiddles, tw[off + (q - 1) ns + k] = W_N^(q k step), FP64 rounded to FP32: W_N^t is the
+// FP64 product of W_N^(t mod 64) and W_N^(64 (t div 64)), 128 sincospi in all instead of one per
+// entry.  scratch: 128 double2 of LDS, free afterwards.  Every thread of the workgroup takes part (at
+// least 128); it ends with a barrier.
+__device__ __forceinline__ void gen_twiddles(float2* tw, double2* scratch, const GPlan& p) {
+  if (threadIdx.x < 128) {
+    const int t = threadIdx.x < 64 ? threadIdx.x : 64 * (threadIdx.x - 64);
+    double s, c;
+    sincospi(2.0 * (double)t / (double)p.n, &s, &c);
+    scratch[threadIdx.x] = make_double2(c, -s);
+  }
+  __syncthreads();
+  for (int s = 1; s < p.np; ++s) {
+    const GPass& g = p.p[s];
+    const int ne = g.ns * (g.r - 1);
+    for (int e = threadIdx.x; e < ne; e += blockDim.x) {
+      const int q1 = gdiv(e, g.mns), k = e - q1 * g.ns;
+      const int t = (q1 + 1) * k * g.step;  // below n
+      const double2 a = scratch[t & 63], b = scratch[64 + (t >> 6)];
+      tw[g.off + e] = make_float2((float)(a.x * b.x - a.y * b.y), (float)(a.x * b.y + a.y * b.x));
+    }
+  }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------------------------
 // length-R DFTs in registers (forward sign), natural order in and out
-__device__ __forceinline__ void gdft2(float2* v) {
-  const float2 a = v[0], b = v[1];
-  v[0] = cadd(a, b);
-  v[1] = csub(a, b);
-}
-
-__device__ __forceinline__ void gdft4(float2* v) {
-  const float2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]), t2 = cadd(v[1], v[3]), t3 = csub(v[1], v[3]);
-  v[0] = cadd(t0, t2);
-  v[2] = csub(t0, t2);
-  v[1] = cadd(t1, cmul_mi(t3));
-  v[3] = csub(t1, cmul_mi(t3));
-}
 
 // X_k = sum_n x_n exp(-2 pi i n k / 3): with s = x1 + x2, d = x1 - x2,
 // X_0 = x0 + s, X_{1,2} = x0 - s/2 -/+ i (sqrt(3)/2) d
@@ -97,61 +183,165 @@ __device__ __forceinline__ void gdft5(float2* v) {
   v[3] = make_float2(p2.x - q2.y, p2.y + q2.x);
 }
 
-// One Stockham pass of radix R over rb rows of length n at buf[row * n + i] (blockDim.x ==
-// kGenThreads).  The twiddle exponent q (j mod Ns) n/(Ns R) is below n.
-template <int R>
-__device__ __forceinline__ void gen_pass(float2* buf, const float2* tw, int n, int rb, int ns) {
-  const int m = n / R;               // butterflies per row
-  const int tstride = n / (ns * R);  // twiddle index step of exponent 1
-  const int total = rb * m;
-  // butterflies per thread: rb n <= kGenMax elements make at most kGenMax / R butterflies
-  constexpr int kMaxB = (kGenMax / R + kGenThreads - 1) / kGenThreads;
-  float2 v[kMaxB][R];
+// length 9 = 3 x 3 (n = n1 + 3 n2, X[k2 + 3 k1]), the inner twiddles exp(-2 pi i n1 k2 / 9)
+__device__ __forceinline__ void gdft9(float2* v) {
+  const float2 w1 = make_float2(0.76604444311897803520f, -0.64278760968653932632f);   // 2 pi/9
+  const float2 w2 = make_float2(0.17364817766693034885f, -0.98480775301220805937f);   // 4 pi/9
+  const float2 w4 = make_float2(-0.93969262078590838405f, -0.34202014332566873304f);  // 8 pi/9
+  float2 y[3][3];
 #pragma unroll
-  for (int b = 0; b < kMaxB; ++b) {
-    const int g = threadIdx.x + b * kGenThreads;
-    if (g < total) {
-      const int row = g / m, j = g % m;
-      const float2* in = buf + row * n;
-      const int k = j % ns;
+  for (int a = 0; a < 3; ++a) {
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        float2 x = in[j + q * m];
-        if (q > 0 && ns > 1) x = cmul(x, tw[q * k * tstride]);
-        v[b][q] = x;
-      }
-      if constexpr (R == 2) gdft2(v[b]);
-      else if constexpr (R == 3) gdft3(v[b]);
-      else if constexpr (R == 4) gdft4(v[b]);
-      else gdft5(v[b]);
-    }
+    for (int b = 0; b < 3; ++b) y[a][b] = v[a + 3 * b];
+    gdft3(y[a]);
   }
-  __syncthreads();
+  y[1][1] = cmul(y[1][1], w1);
+  y[1][2] = cmul(y[1][2], w2);
+  y[2][1] = cmul(y[2][1], w2);
+  y[2][2] = cmul(y[2][2], w4);
 #pragma unroll
-  for (int b = 0; b < kMaxB; ++b) {
-    const int g = threadIdx.x + b * kGenThreads;
-    if (g < total) {
-      const int row = g / m, j = g % m;
-      float2* out = buf + row * n;
-      const int base = (j / ns) * ns * R + (j % ns);
+  for (int k = 0; k < 3; ++k) {
+    float2 c[3] = {y[0][k], y[1][k], y[2][k]};
+    gdft3(c);
 #pragma unroll
-      for (int q = 0; q < R; ++q) out[base + q * ns] = v[b][q];
-    }
+    for (int b = 0; b < 3; ++b) v[k + 3 * b] = c[b];
   }
-  __syncthreads();
 }
 
-// Forward FFT of rb rows of length p.n in buf (LDS), in place; tw from gen_twiddles.
-__device__ __forceinline__ void gen_fft(float2* buf, const float2* tw, const GPlan& p, int rb) {
-  int ns = 1;
-  for (int s = 0; s < p.np; ++s) {
-    const int r = p.r[s];
-    if (r == 4) gen_pass<4>(buf, tw, p.n, rb, ns);
-    else if (r == 2) gen_pass<2>(buf, tw, p.n, rb, ns);
-    else if (r == 3) gen_pass<3>(buf, tw, p.n, rb, ns);
-    else gen_pass<5>(buf, tw, p.n, rb, ns);
-    ns *= r;
+template <int R>
+__device__ __forceinline__ void gdft(float2* v);
+
+// length A B, A and B coprime, by the prime-factor map: input n = (B a + A b) mod AB, output k with
+// k mod A = ka and k mod B = kb; exp(-2 pi i n k / AB) = exp(-2 pi i a ka / A) exp(-2 pi i b kb / B)
+template <int A, int B>
+__device__ __forceinline__ void gdft_pfa(float2* v) {
+  constexpr int N = A * B;
+  float2 y[B][A];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+#pragma unroll
+    for (int a = 0; a < A; ++a) y[b][a] = v[(B * a + A * b) % N];
+    gdft<A>(y[b]);
   }
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+    float2 c[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) c[b] = y[b][a];
+    gdft<B>(c);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (k % A == a) v[k] = c[k % B];
+  }
+}
+
+template <int R>
+__device__ __forceinline__ void gdft(float2* v) {
+  if constexpr (R == 2) dft2(v);
+  else if constexpr (R == 3) gdft3(v);
+  else if constexpr (R == 4) dft4(v);
+  else if constexpr (R == 5) gdft5(v);
+  else if constexpr (R == 6) gdft_pfa<2, 3>(v);
+  else if constexpr (R == 8) dft8(v);
+  else if constexpr (R == 9) gdft9(v);
+  else if constexpr (R == 10) gdft_pfa<2, 5>(v);
+  else if constexpr (R == 12) gdft_pfa<4, 3>(v);
+  else if constexpr (R == 15) gdft_pfa<3, 5>(v);
+  else dft16(v);
+}
+
+// f(integral_constant R) for a plan's radix r (the same for the whole workgroup)
+template <typename F>
+__device__ __forceinline__ void gen_radix(int r, F&& f) {
+  switch (r) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 9: f(std::integral_constant<int, 9>{}); break;
+    case 10: f(std::integral_constant<int, 10>{}); break;
+    case 12: f(std::integral_constant<int, 12>{}); break;
+    case 15: f(std::integral_constant<int, 15>{}); break;
+    default: f(std::integral_constant<int, 16>{}); break;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The parts of a pass of radix R over rb rows of the workgroup (T threads, EPT registers per thread):
+// thread t takes butterflies g = t + T b < rb m, of row g / m, held at v[b R ..].
+
+// The thread index, opaque to the compiler: a pass's index arithmetic depends on nothing that changes
+// from tile to tile, and hoisted out of the tile loop (for every radix of the switch) it spills
+// hundreds of registers.
+__device__ __forceinline__ int gen_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+template <int R, int EPT, int T, typename F>
+__device__ __forceinline__ void gen_each(int tid, const GPass& p, int rb, F&& f) {
+  const int total = rb * p.m;
+#pragma unroll
+  for (int b = 0; b < gen_per_thread(R, EPT); ++b) {
+    const int g = tid + b * T;
+    if (g < total) {
+      const int row = gdiv(g, p.mm);
+      f(b, row, g - row * p.m);
+    }
+  }
+}
+
+// inputs from LDS
+template <int R, int EPT, int T>
+__device__ __forceinline__ void gen_read(int tid, float2* v, const float2* buf, int stride, const GPass& p, int rb) {
+  gen_each<R, EPT, T>(tid, p, rb, [&](int b, int row, int j) {
+    const float2* in = buf + row * stride;
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[b * R + q] = in[gpad(j + q * p.m)];
+  });
+}
+
+// twiddles (TW: not the first pass) and the length-R DFTs
+template <int R, int EPT, int T, bool TW>
+__device__ __forceinline__ void gen_compute(int tid, float2* v, const float2* tw, const GPass& p, int rb) {
+  gen_each<R, EPT, T>(tid, p, rb, [&](int b, int, int j) {
+    if constexpr (TW) {
+      const float2* w = tw + p.off + (j - gdiv(j, p.mns) * p.ns);
+#pragma unroll
+      for (int q = 1; q < R; ++q) v[b * R + q] = cmul(v[b * R + q], w[(q - 1) * p.ns]);
+    }
+    gdft<R>(v + b * R);
+  });
+}
+
+// outputs to LDS
+template <int R, int EPT, int T>
+__device__ __forceinline__ void gen_write(int tid, const float2* v, float2* buf, int stride, const GPass& p, int rb) {
+  gen_each<R, EPT, T>(tid, p, rb, [&](int b, int row, int j) {
+    float2* out = buf + row * stride;
+    const int hi = gdiv(j, p.mns);
+    const int base = hi * p.ns * (R - 1) + j;  // (j div ns) ns R + j mod ns
+#pragma unroll
+    for (int q = 0; q < R; ++q) out[gpad(base + q * p.ns)] = v[b * R + q];
+  });
+}
+
+// A whole pass in place (TW: not the first), ending with a barrier; the caller has a barrier before it.
+template <int EPT, int T, bool TW>
+__device__ __forceinline__ void gen_pass(float2* buf, int stride, const float2* tw, const GPass& p, int rb) {
+  gen_radix(p.r, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    const int tid = gen_tid();
+    float2 v[R * gen_per_thread(R, EPT)];
+    gen_read<R, EPT, T>(tid, v, buf, stride, p, rb);
+    gen_compute<R, EPT, T, TW>(tid, v, tw, p, rb);
+    __syncthreads();
+    gen_write<R, EPT, T>(tid, v, buf, stride, p, rb);
+  });
+  __syncthreads();
 }
 
 }  // namespace stem

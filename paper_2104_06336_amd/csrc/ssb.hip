@@ -17,6 +17,7 @@
 #include "fft_generic.h"
 #include "fft_wave.h"
 #include "ssb_fused.h"
+#include "ssb_gen.h"
 #include "ssb_pruned.h"
 #include "kernels.h"
 #include "optics.h"
@@ -36,18 +37,16 @@ struct SsbLayout {
   int64_t F;
   bool store;     // STEM_G_STORE
   int xpix;       // pixels whose row-transformed columns the X region holds (n_k, or one chunk)
-  int ypix;       // pixels of the column-transform scratch (stored G of the other lengths), or 0
   int nchunks;    // pixel chunks of a sum
   int64_t pcap;   // entries of the pruned G array (0 without STEM_G_STORE)
-  size_t rows, kc, kchi, cst, cmask, lut, stats, npq, D, X, Y, poff, ptot, pg, T, A, Tb, pdc, pdth, part, wcnt, pws, pcs,
+  size_t rows, kc, kchi, cst, cmask, lut, stats, npq, D, X, poff, ptot, pg, T, A, Tb, pdc, pdth, part, wcnt, pws, pcs,
       total;
   int nmw;      // 64-bit words per column set of the active-pixel mask
-  int groups;   // pixel groups of the fused column kernels (the same for every chunk)
+  int groups;   // pixel groups of the fused column sum (the same for every chunk)
   int pgroups;  // pixel groups of the kernels over the stored double-overlap values
   int ncs;      // column sets (colset_width(Ny) half-spectrum columns each)
   bool fast;    // both scan lengths taken by the fused kernels (powers of two in [32, 1024])
-  int64_t nwy;  // waves of the fused kernels
-  int64_t nwp;  // waves of the refocus sum over the full columns of G (other scan lengths)
+  int64_t nwy;  // waves of the fused column sum (and, for the fast lengths, of the fused adjoint)
   int64_t nws;  // pieces the refocus sum over the stored values aims at
   int64_t nwq;  // STEM_G_STORE: waves (at most) of the refocus sum over the stored values
   int64_t part_rows;  // rows of Ny values the partial-sum buffer holds
@@ -111,13 +110,11 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     L->nchunks = (n_k + nc - 1) / nc;
     chunk = (n_k + L->nchunks - 1) / L->nchunks;
   }
-  L->ypix = 0;
   if (L->store) {
-    // every pixel's row transform; the other lengths also transform the columns in chunks into a
-    // scratch of their own (the row transform stays for the panel of G)
+    // every pixel's row transform (it also serves the panel of G), summed in one go; the other
+    // lengths take the pixels in chunks of a scratch size the caller sets
     L->xpix = n_k;
-    if (L->fast) L->nchunks = 1;
-    else L->ypix = chunk;
+    if (L->fast || ssb.scratch_mib == 0) L->nchunks = 1;
     L->pcap = pruned_bound(scan, op, n_k);
   } else {
     L->xpix = chunk;
@@ -140,7 +137,6 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
   L->npq = o;   o = align256(o + sizeof(int32_t) * (size_t)L->F);
   L->D = o;     o = align256(o + (size_t)n_k * L->F * (ssb.d_bits / 8));
   L->X = o;     o = align256(o + (size_t)L->xpix * per_pixel);
-  L->Y = o;     o = align256(o + (size_t)L->ypix * per_pixel);
   L->poff = o;  o = align256(o + (L->store ? sizeof(int64_t) * ((size_t)n_k * scan.nx + 1) : 0));
   L->ptot = o;  o = align256(o + (L->store ? sizeof(int64_t) * (size_t)scan.nx : 0));
   L->pg = o;    o = align256(o + sizeof(float2) * (size_t)L->pcap);
@@ -149,11 +145,11 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
   L->Tb = o;    o = align256(o + (size_t)L->F * sizeof(float2));
   // pixel groups: the same for every chunk (the partial sums of a later chunk add to the same
   // waves' partials), so at most the smallest chunk's pixel count
-  int g = yreduce_groups(scan.ny, scan.nx, n_k);
   const int smallest = n_k / L->nchunks;
+  int g = L->fast ? yreduce_groups(scan.ny, scan.nx, n_k) : gsum_groups(scan.ny, scan.nx, n_k, L->nchunks > 1);
   if (g > smallest) g = smallest;
   L->groups = g < 1 ? 1 : g;
-  L->nwy = (int64_t)((L->ncs + 3) / 4) * 4 * L->groups;
+  L->nwy = L->fast ? (int64_t)((L->ncs + 3) / 4) * 4 * L->groups : gsum_waves(scan.ny, scan.nx, L->groups);
   // the kernels over the stored values: a wave (refocus) or workgroup (adjoint) per column of the
   // whole plane and pixel group, about kPrunedBlocks of them, at most the fused kernels' partial
   // sums
@@ -163,7 +159,6 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     pg = pg > n_k ? n_k : pg;
     pg = pg > gmax ? gmax : pg;
     L->pgroups = pg < 1 ? 1 : pg;
-    L->nwp = psum_launch_waves(scan.ny, scan.nx, L->pgroups);
     L->nwa = padj_partials(scan.nx, L->pgroups);
     // the balanced pieces: as many as the GPU holds waves at once (more, one per column with
     // pairs, when the columns outnumber them)
@@ -172,8 +167,7 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     L->nws = nws;
     L->nwq = L->store ? ((nws > scan.nx ? nws : scan.nx) + w - 1) / w * w : 0;
   }
-  int64_t nw = L->nwy > L->nwp ? L->nwy : L->nwp;
-  nw = nw > L->nwq ? nw : L->nwq;
+  int64_t nw = L->nwy > L->nwq ? L->nwy : L->nwq;
   nw = nw > L->nwa ? nw : L->nwa;
   const int rows = L->ncs > scan.nx ? L->ncs : scan.nx;
   const int parts = L->groups > L->pgroups ? L->groups : L->pgroups;
@@ -538,7 +532,6 @@ struct Bufs {
   int32_t* npq;
   void* D;
   float2* X;
-  float2* Y;
   int64_t* poff;
   int64_t* ptot;
   float2* pg;
@@ -563,7 +556,7 @@ static Bufs carve(void* state, const SsbLayout& L) {
   char* p = (char*)state;
   return Bufs{(RowRun*)(p + L.rows), (double2*)(p + L.kc), (double*)(p + L.kchi), (int4*)(p + L.cst),
               (uint64_t*)(p + L.cmask), (int16_t*)(p + L.lut), (unsigned long long*)(p + L.stats),
-              (int32_t*)(p + L.npq), (void*)(p + L.D), (float2*)(p + L.X), (float2*)(p + L.Y), (int64_t*)(p + L.poff),
+              (int32_t*)(p + L.npq), (void*)(p + L.D), (float2*)(p + L.X), (int64_t*)(p + L.poff),
               (int64_t*)(p + L.ptot), (float2*)(p + L.pg), (float2*)(p + L.T), (float2*)(p + L.A), (float2*)(p + L.Tb),
               (double*)(p + L.pdc), (float*)(p + L.pdth), (float2*)(p + L.part),
               (unsigned long long*)(p + L.wcnt), (PieceTab*)(p + L.pws), (int64_t*)(p + L.pcs)};
@@ -640,27 +633,19 @@ static int xstage_pixels(const SsbLayout& L, const Bufs& b, const stem_ssb& ssb,
                                    s);
 }
 
-// The other scan lengths: row transform of the pixels [k0, k1) (all rows) into X by the generic
-// FFT (one real row per transform), then the column transforms of those pixels, from src into dst
-// (in place when equal).
+// The other scan lengths: row transform of the pixels [k0, k1) (all rows) into x, and (for the
+// adjoint) the column transforms of those pixels in place.
 static int xstage_generic(const SsbLayout& L, const Bufs& b, const stem_ssb& ssb, int ny, int nx, int k0, int k1,
-                          hipStream_t s) {
-  RowFftArgs a{};
-  a.nrows = (int64_t)(k1 - k0) * ny;
-  a.in_u = ssb.d_bits == 8 ? (const void*)((const uint8_t*)b.D + (size_t)k0 * L.F)
-                           : (const void*)((const uint16_t*)b.D + (size_t)k0 * L.F);
-  a.out_c = b.X;
-  a.xrows = ny;
-  a.osc = make_float2(1.f, 0.f);
-  a.tag = "xstage_fft";
-  return launch_row_fft(nx, false, ssb.d_bits == 8 ? IN_U8 : IN_U16, OUT_X, a, s);
+                          float2* x, hipStream_t s) {
+  return launch_gen_x(nx, (const uint8_t*)b.D + (size_t)k0 * L.F * (ssb.d_bits / 8), ssb.d_bits, ny,
+                      (int64_t)(k1 - k0) * ny, x, s);
 }
 
-static int colfft_generic(const SsbLayout& L, int ny, int k0, int k1, const float2* src, float2* dst, hipStream_t s) {
+static int colfft_generic(const SsbLayout& L, int ny, int k0, int k1, float2* x, hipStream_t s) {
   RowFftArgs a{};
   a.nrows = (int64_t)(k1 - k0) * L.nh;
-  a.in_c = src;
-  a.out_c = dst;
+  a.in_c = x;
+  a.out_c = x;
   a.osc = make_float2(1.f, 0.f);
   a.tag = "ystage_fft";
   return launch_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s);
@@ -859,31 +844,22 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
     return run_phase(L, b, *scan, L.pgroups, L.nwq, 1, ssb->normalize ? b.npq : nullptr, d_phase, d_T, s, false,
                      b.pcs);
   } else if (!L.fast) {
-    // the other scan lengths: row and column transforms by the generic FFT, then Eq. 3 per
-    // (pixel, column) run over the full columns of G, chunk by chunk
-    a.ngroups = L.pgroups;
-    if (L.store) {
-      if ((st = xstage_generic(L, b, *ssb, ny, nx, 0, n_k, s))) return st;
-      if ((st = run_prune_offsets(L, b, nx, d_status, s))) return st;
-    }
+    // the other scan lengths: row transforms, then the column transforms fused with Eq. 3, chunk by
+    // chunk
+    if (L.store && (st = run_prune_offsets(L, b, nx, d_status, s))) return st;
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
       chunk_range(L, ch, k0, k1);
-      if (L.store) {
-        if ((st = colfft_generic(L, ny, k0, k1, b.X + (size_t)k0 * L.nh * ny, b.Y, s))) return st;
-        a.X = b.Y;
-      } else {
-        if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, s))) return st;
-        if ((st = colfft_generic(L, ny, k0, k1, b.X, b.X, s))) return st;
-      }
+      // STEM_G_STORE keeps every pixel's columns, the other mode one chunk's
+      float2* x = L.store ? b.X + (size_t)k0 * L.nh * ny : b.X;
+      if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, x, s))) return st;
+      a.X = x;
       a.xk0 = k0;
       a.k0 = k0;
       a.k1 = k1;
       a.accumulate = ch > 0;
-      if ((st = launch_psum(ny, a, o, chi0, L.store, s))) return st;
+      if ((st = launch_gsum(ny, a, o, chi0, L.store, s))) return st;
     }
-    return run_phase(L, b, *scan, L.pgroups, L.nwp, L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase, d_T, s,
-                     !refocus);
   } else if (L.store) {
     if ((st = run_prune_offsets(L, b, nx, d_status, s))) return st;
     if ((st = launch_yreduce(ssb->precision, ny, a, o, chi0, 1, s))) return st;
@@ -900,7 +876,7 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
       if ((st = launch_yreduce(ssb->precision, ny, a, o, chi0, 0, s))) return st;
     }
   }
-  return run_phase(L, b, *scan, L.groups, L.nwy, L.store ? 1 : L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase,
+  return run_phase(L, b, *scan, L.groups, L.nwy, L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase,
                    d_T, s, !refocus);
 }
 
@@ -1215,8 +1191,8 @@ extern "C" int ssb_backward(const float* d_dLdphi, const stem_det* det, const st
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
       chunk_range(L, ch, k0, k1);
-      if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, s))) return st;
-      if ((st = colfft_generic(L, ny, k0, k1, b.X, b.X, s))) return st;
+      if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, b.X, s))) return st;
+      if ((st = colfft_generic(L, ny, k0, k1, b.X, s))) return st;
       y.xk0 = k0;
       y.k0 = k0;
       y.k1 = k1;

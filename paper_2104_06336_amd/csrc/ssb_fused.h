@@ -231,10 +231,12 @@ __global__ void __launch_bounds__(64 * XF::kXWaves) k_xstage(const DT* __restric
 // The sets of one pixel for a half-spectrum column c (direct) and for -c (mirror) depend only on
 // the geometry; they are tabulated once per reconstruction (k_colsets), 16 bytes per (pixel,
 // column): (a0, a1, b0, b1) direct and mirrored as int16 (|iy| <= 2048).
-__device__ __forceinline__ void load_colsets(const int4* __restrict__ cst, int64_t i, ColSet& d, ColSet& m) {
-  const int4 r = cst[i];
+__device__ __forceinline__ void unpack_colsets(const int4 r, ColSet& d, ColSet& m) {
   d = ColSet{(int)(short)(r.x & 0xffff), r.x >> 16, (int)(short)(r.y & 0xffff), r.y >> 16};
   m = ColSet{(int)(short)(r.z & 0xffff), r.z >> 16, (int)(short)(r.w & 0xffff), r.w >> 16};
+}
+__device__ __forceinline__ void load_colsets(const int4* __restrict__ cst, int64_t i, ColSet& d, ColSet& m) {
+  unpack_colsets(cst[i], d, m);
 }
 
 // Arguments shared by the fused column kernels.
