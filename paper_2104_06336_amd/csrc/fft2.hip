@@ -6,7 +6,9 @@
 // fft_wave.h.  Row-major outputs are stored straight from registers; transposed outputs
 // (element (r, m) -> out[m*stride + r]) are first staged in the waves' LDS buffers so that the
 // workgroup writes runs of W B consecutive rows per frequency.
+#include <memory>
 #include <mutex>
+#include <new>
 
 #include "common.h"
 #include "fft_generic.h"
@@ -249,6 +251,113 @@ static void launch_n(bool inv, const RowFftArgs& a, int in, int out, hipStream_t
 // rows-fastest (runs of RB consecutive rows per frequency).  RB is what LDS holds of 4096 elements,
 // less where that would leave compute units without a workgroup (1000 rows of 1000: 3 rows each).
 
+constexpr int kGenRadices[11] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16};
+
+// The radices of n, ascending, as few as possible (at least two) and then with the smallest sum.
+static void gen_factor(int n, int from, int depth, int* cur, int* best, int& best_np, int& best_sum) {
+  if (n == 1) {
+    int sum = 0;
+    for (int i = 0; i < depth; ++i) sum += cur[i];
+    if (depth >= 2 && (depth < best_np || (depth == best_np && sum < best_sum))) {
+      best_np = depth;
+      best_sum = sum;
+      for (int i = 0; i < depth; ++i) best[i] = cur[i];
+    }
+    return;
+  }
+  if (depth >= kGenMaxPasses || depth >= best_np) return;
+  for (int i = from; i < 11 && kGenRadices[i] <= n; ++i) {
+    if (n % kGenRadices[i]) continue;
+    cur[depth] = kGenRadices[i];
+    gen_factor(n / kGenRadices[i], i, depth + 1, cur, best, best_np, best_sum);
+  }
+}
+
+// Lanes of a group of g that share a bank of 8 bytes (g banks), worst bank, for element positions pos.
+template <typename F>
+static int bank_depth(int g, F&& pos) {
+  int n[32] = {}, most = 0;
+  for (int l = 0; l < g; ++l) {
+    const int k = ++n[pos(l) % g];
+    most = k > most ? k : most;
+  }
+  return most;
+}
+
+// The padding per block of ns r elements of the layout between a pass (ns, r) and the next: the one of
+// at most an eighth of the block (at least 1) whose writes and reads share banks least, over the first 16
+// and 32 lanes.
+static int gen_pad(int ns, int r) {
+  const int blk = ns * r, lim = blk / 8 > 1 ? (blk / 8 < 32 ? blk / 8 : 31) : 1;
+  int best = 0, cost = 1 << 30;
+  for (int w = 0; w <= lim; ++w) {
+    int c = 0;
+    for (int g = 16; g <= 32; g += 16) {
+      c += bank_depth(g, [&](int l) { return l + l / ns * (ns * (r - 1) + w); });
+      c += bank_depth(g, [&](int l) { return l + l / blk * w; });
+    }
+    if (c < cost) {
+      cost = c;
+      best = w;
+    }
+  }
+  return best;
+}
+
+static bool gen_make_plan(int n, GPlan& p) {
+  int cur[kGenMaxPasses], best[kGenMaxPasses], np = kGenMaxPasses + 1, sum = 0;
+  gen_factor(n, 0, 0, cur, best, np, sum);
+  if (np > kGenMaxPasses) return false;
+  p.n = n;
+  p.np = np;
+  p.ntw = n - best[0];
+  p.len = n;
+  p.mn = gmagic(n);
+  int ns = 1, rp = 0;
+  for (int s = 0; s < np; ++s) {
+    GPass& q = p.p[s];
+    q.r = best[s];
+    q.m = n / q.r;
+    q.ns = ns;
+    q.off = s ? ns - best[0] : 0;  // passes 1 .. s-1 hold ns (r - 1) entries each
+    q.step = n / (ns * q.r);
+    q.rp = rp;
+    q.rq = q.m + q.m / ns * rp;
+    q.wp = s < np - 1 ? gen_pad(ns, q.r) : 0;
+    q.mm = gmagic(q.m);
+    q.mns = gmagic(q.ns);
+    ns *= q.r;
+    rp = q.wp;
+    p.len = n + n / ns * rp > p.len ? n + n / ns * rp : p.len;
+  }
+  return true;
+}
+
+bool gen_plan(int n, GPlan& p) {
+  if (n < 4 || n > kGenMax) return false;
+  static std::mutex mu;
+  static std::unique_ptr<GPlan> plans[kGenMax + 1];
+  {
+    int m = n;
+    while (m % 2 == 0) m /= 2;
+    while (m % 3 == 0) m /= 3;
+    while (m % 5 == 0) m /= 5;
+    if (m != 1) return false;
+  }
+  std::lock_guard<std::mutex> lk(mu);
+  if (!plans[n]) {
+    GPlan q;
+    if (!gen_make_plan(n, q)) return false;
+    plans[n].reset(new (std::nothrow) GPlan(q));
+    if (!plans[n]) {
+      p = q;
+      return true;
+    }
+  }
+  p = *plans[n];
+  return true;
+}
+
 bool scan_length_ok(int n) {
   if (fast_length(n)) return true;
   GPlan p;
@@ -260,7 +369,7 @@ constexpr int kGenEpt = 30;  // registers (complex) of a thread of the row passe
 __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p, int rb, int inv, int in_mode,
                                                           int out_mode) {
   extern __shared__ __align__(16) float2 s_g[];  // twiddles, then rb rows
-  const int n = p.n, stride = gen_stride(n);
+  const int n = p.n, stride = p.len;
   float2* tw = s_g;
   float2* buf = s_g + gen_tw_size(p);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -334,7 +443,7 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
           x.y = a.in_d1 ? (float)(a.in_d1[el] * (double)a.s1) : 0.f;
         }
       }
-      buf[rl * stride + gpad(i)] = inv ? cconj(x) : x;
+      buf[rl * stride + i] = inv ? cconj(x) : x;
     }
     __syncthreads();
     gen_pass<kGenEpt, kGenThreads, false>(buf, stride, tw, p.p[0], rb);
@@ -348,7 +457,7 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
       const int rl = transposed ? e - hi * rb : hi, m = transposed ? hi : e - hi * n;
       const int64_t r = r0 + rl;
       if (r >= a.nrows) continue;
-      const float2 y = buf[rl * stride + gpad(m)];
+      const float2 y = buf[rl * stride + m];
       const float2 v = cmul(inv ? cconj(y) : y, a.osc);
       if (out_mode == OUT_ROW_C64) a.out_c[r * n + m] = v;
       else if (out_mode == OUT_ROW_RE) a.out_f[r * n + m] = v.x;
@@ -369,7 +478,7 @@ static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFf
   if (rb > a.nrows / 256) rb = a.nrows / 256;
   if (rb < 1) rb = 1;
   const int64_t batches = (a.nrows + rb - 1) / rb;
-  const size_t lds = gen_lds(p, (int)rb, gen_stride(n));
+  const size_t lds = gen_lds(p, (int)rb, p.len);
   const int res = resident_blocks((const void*)k_grow_fft, kGenThreads, lds);
   const int64_t cap = res > 0 ? res : 1024;
   hipLaunchKernelGGL(k_grow_fft, dim3((unsigned)(batches < cap ? batches : cap)), dim3(kGenThreads), lds, stream, a,
@@ -386,11 +495,13 @@ static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFf
 // neighbouring counts).  Workgroups of 512 threads with up to 64 KB of rows, two per compute unit;
 // RB is a power of two, so that a thread keeps its row pair through the write loop.
 //
-// Bound by LDS traffic and the writes of X.  Measured (one MI355X): 1000 x 1000 scan, 176 pixels of
-// 8-bit counts, 473 us against 1640 us for one real row per complex transform written in runs of four;
-// 96 x 160, 793 pixels of 16-bit counts, 25 us against 159 us.
+// Bound by vector arithmetic and latency (VALU busy 0.64).  Measured (one MI355X): 1000 x 1000 scan, 176
+// pixels of 8-bit counts, 299 us against 1640 us for one real row per complex transform written in runs of
+// four; 96 x 160, 793 pixels of 16-bit counts, 26 us against 159 us.  Without the next tile's counts in
+// flight and with rows padded per 16 elements (three operations per LDS address, twice the bank
+// conflicts) the first took 473 us.
 constexpr int kGenXThreads = 512;
-constexpr int kGenXEpt = 24;
+constexpr int kGenXEpt = 20;
 
 template <typename DT>
 __global__ void __launch_bounds__(kGenXThreads, 4) k_grow_x(const DT* __restrict__ D, GPlan p, int lrb, int stride,
@@ -401,28 +512,43 @@ __global__ void __launch_bounds__(kGenXThreads, 4) k_grow_x(const DT* __restrict
   float2* tw = s_g;
   float2* buf = s_g + gen_tw_size(p);
   gen_twiddles(tw, (double2*)buf, p);
+  const GPass p0 = p.p[0];
   const uint32_t tr = 2u << lrb, ntiles = (nrows + tr - 1) / tr;
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint32_t r0 = tile * tr;
-    gen_radix(p.p[0].r, [&](auto rc) {
+  // the first pass's counts of a tile (rows 2p and 2p + 1), loaded while the tile before is
+  // transformed and written
+  DT ca[kGenXEpt], cb[kGenXEpt];
+  auto load = [&](uint32_t tile) {
+    gen_radix(p0.r, [&](auto rc) {
       constexpr int R = decltype(rc)::value;
-      const int tid = gen_tid();
-      float2 v[R * gen_per_thread(R, kGenXEpt)];
-      gen_each<R, kGenXEpt, kGenXThreads>(tid, p.p[0], rb, [&](int b, int row, int j) {
-        const uint32_t r = r0 + 2 * row;  // nrows is even
+      gen_each<R, kGenXEpt, kGenXThreads>(gen_tid(), p0, rb, [&](int b, int row, int j) {
+        const uint32_t r = min(tile * tr + 2 * row, nrows - 2);  // nrows is even; rows past it are not written
         const DT* src = D + (int64_t)r * n + j;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-          float2 x = make_float2(0.f, 0.f);
-          if (r < nrows) x = make_float2((float)src[q * p.p[0].m], (float)src[n + q * p.p[0].m]);
-          v[b * R + q] = x;
+          ca[b * R + q] = src[q * p0.m];
+          cb[b * R + q] = src[n + q * p0.m];
         }
       });
-      gen_compute<R, kGenXEpt, kGenXThreads, false>(tid, v, tw, p.p[0], rb);
-      gen_write<R, kGenXEpt, kGenXThreads>(tid, v, buf, stride, p.p[0], rb);
     });
+  };
+  if (blockIdx.x < ntiles) load(blockIdx.x);
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t r0 = tile * tr;
+    gen_radix(p0.r, [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      const int tid = gen_tid();
+      float2 v[R * gen_per_thread(R, kGenXEpt)];
+#pragma unroll
+      for (int e = 0; e < R * gen_per_thread(R, kGenXEpt); ++e) v[e] = make_float2((float)ca[e], (float)cb[e]);
+      gen_compute<R, kGenXEpt, kGenXThreads, false>(tid, v, tw, p0, rb);
+      gen_write<R, kGenXEpt, kGenXThreads>(tid, v, buf, stride, p0, rb);
+    });
+    if (tile + gridDim.x < ntiles) load(tile + gridDim.x);
     __syncthreads();
-    for (int s = 1; s < p.np; ++s) gen_pass<kGenXEpt, kGenXThreads, true>(buf, stride, tw, p.p[s], rb);
+    for (int s = 1; s < p.np; ++s) {
+      const GPass ps = p.p[s];
+      gen_pass<kGenXEpt, kGenXThreads, true>(buf, stride, tw, ps, rb);
+    }
     // z = a + i b of rows (2p, 2p+1): A(m) = (z(m) + conj z(-m))/2, B(m) = (z(m) - conj z(-m))/(2i)
     const int pr = (int)threadIdx.x & (rb - 1);
     const uint32_t r = r0 + 2 * pr;
@@ -431,7 +557,7 @@ __global__ void __launch_bounds__(kGenXThreads, 4) k_grow_x(const DT* __restrict
       float2* out = X + (int64_t)kd * nh * ny + ry;
       const float2* z = buf + pr * stride;
       for (int m = (int)threadIdx.x >> lrb; m < nh; m += kGenXThreads >> lrb) {
-        const float2 u = z[gpad(m)], w = cconj(z[gpad(m ? n - m : 0)]);
+        const float2 u = z[m], w = cconj(z[m ? n - m : 0]);
         const float2 va = cscale(cadd(u, w), 0.5f), vb = cscale(cmul_mi(csub(u, w)), 0.5f);
         *(float4*)(out + (int64_t)m * ny) = make_float4(va.x, va.y, vb.x, vb.y);
       }
@@ -448,12 +574,12 @@ int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2
   // compute unit still gets two workgroups
   const int most = gen_max_rows(p, kGenXThreads, kGenXEpt);
   int lrb = 0;
-  while ((2 << lrb) <= most && (2 << lrb) * gen_stride(n) <= 8704 &&
+  while ((2 << lrb) <= most && (2 << lrb) * p.len <= 8704 &&
          ((2 << lrb) <= 8 || nrows >= (4ll << lrb) * 512))
     ++lrb;
   // the row stride: 1 / rb of the banks apart modulo the 32 of 8 bytes, so that the rb rows of one
   // frequency, read together by the split, lie in different banks
-  int stride = gen_stride(n);
+  int stride = p.len;
   const int step = 32 >> lrb ? 32 >> lrb : 1;
   while (lrb && (stride & 31) != step) ++stride;
   const size_t lds = gen_lds(p, 1 << lrb, stride);

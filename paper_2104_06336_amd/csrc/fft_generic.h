@@ -28,9 +28,11 @@ constexpr int kGenThreads = 256;  // threads of a generic-FFT workgroup of the r
 constexpr int kGenMaxPasses = 6;
 
 // One pass: radix r, m = n/r, ns the product of the earlier radices, off the pass's first twiddle,
-// step = n/(ns r); mm and mns divide by m and ns (gdiv).
+// step = n/(ns r); mm and mns divide by m and ns (gdiv).  LDS layouts: the pass reads element i of a row
+// at i + (i div ns) rp and writes it at i + (i div (ns r)) wp (the next pass's rp), so that the element of
+// q is a constant away from that of q - 1 on both sides (rq = m + (m div ns) rp apart read, ns written).
 struct GPass {
-  int32_t r, m, ns, off, step;
+  int32_t r, m, ns, off, step, rp, rq, wp;
   uint32_t mm, mns;
 };
 
@@ -38,6 +40,7 @@ struct GPlan {
   int32_t n;
   int32_t np;
   int32_t ntw;  // twiddles of the passes after the first: n - r0
+  int32_t len;  // LDS elements of a row in its longest layout
   uint32_t mn;  // divides by n
   GPass p[kGenMaxPasses];
 };
@@ -47,57 +50,11 @@ struct GPlan {
 inline uint32_t gmagic(int d) { return d == 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
 __device__ __forceinline__ int gdiv(int x, uint32_t mag) { return mag ? (int)__umulhi((uint32_t)x, mag) : x; }
 
-constexpr int kGenRadices[11] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16};
-
-// The radices of n, ascending, as few as possible and then with the smallest sum (balanced); false
-// when n is no product of them.
-inline bool gen_factor(int n, int from, int depth, int* cur, int* best, int& best_np, int& best_sum) {
-  if (n == 1) {
-    int sum = 0;
-    for (int i = 0; i < depth; ++i) sum += cur[i];
-    if (depth >= 2 && (depth < best_np || (depth == best_np && sum < best_sum))) {
-      best_np = depth;
-      best_sum = sum;
-      for (int i = 0; i < depth; ++i) best[i] = cur[i];
-    }
-    return true;
-  }
-  if (depth >= kGenMaxPasses || depth >= best_np) return false;
-  for (int i = from; i < 11; ++i) {
-    const int r = kGenRadices[i];
-    if (r > n) break;
-    if (n % r) continue;
-    cur[depth] = r;
-    gen_factor(n / r, i, depth + 1, cur, best, best_np, best_sum);
-  }
-  return best_np <= kGenMaxPasses;
-}
-
-// The plan of n = 2^a 3^b 5^c, 4 <= n <= kGenMax (at least two passes); false otherwise.  The largest
-// radix is the last pass's: its butterflies are the fewest, at most one per thread in the fused sum.
-inline bool gen_plan(int n, GPlan& p) {
-  if (n < 4 || n > kGenMax) return false;
-  int cur[kGenMaxPasses], best[kGenMaxPasses], np = kGenMaxPasses + 1, sum = 0;
-  gen_factor(n, 0, 0, cur, best, np, sum);
-  if (np > kGenMaxPasses) return false;
-  p.n = n;
-  p.np = np;
-  p.ntw = n - best[0];
-  p.mn = gmagic(n);
-  int ns = 1;
-  for (int s = 0; s < np; ++s) {
-    GPass& q = p.p[s];
-    q.r = best[s];
-    q.m = n / q.r;
-    q.ns = ns;
-    q.off = s ? ns - best[0] : 0;  // passes 1 .. s-1 hold ns (r - 1) entries each
-    q.step = n / (ns * q.r);
-    q.mm = gmagic(q.m);
-    q.mns = gmagic(q.ns);
-    ns *= q.r;
-  }
-  return true;
-}
+// The plan of n = 2^a 3^b 5^c, 4 <= n <= kGenMax: radices ascending, the fewest passes (at least two) and
+// then the smallest sum; the largest radix is the last pass's, whose butterflies are the fewest, at
+// most one per thread in the fused sum.  False for other lengths.  A length's plan is formed once and
+// kept (about a hundred lengths exist).
+bool gen_plan(int n, GPlan& p);
 
 // Butterflies of radix r a thread takes in a pass with ept registers, and the rows of a workgroup of
 // t threads that respect it in every pass.
@@ -110,11 +67,6 @@ inline int gen_max_rows(const GPlan& p, int threads, int ept) {
   }
   return rb;
 }
-
-// LDS position of element i of a row (one element of padding per 16: the strides Ns of the passes'
-// writes are often multiples of 8 or 16) and the row stride.
-__host__ __device__ __forceinline__ int gpad(int i) { return i + (i >> 4); }
-__host__ __device__ inline int gen_stride(int n) { return gpad(n - 1) + 1; }
 
 // LDS of a workgroup in float2: the twiddles (an even number of entries, so that what follows is
 // 16-byte aligned), then the rows (at least the 128 double2 that gen_twiddles works in)
@@ -250,8 +202,8 @@ __device__ __forceinline__ void gdft(float2* v) {
   else dft16(v);
 }
 
-// f(integral_constant R) for a plan's radix r (the same for the whole workgroup)
-template <typename F>
+// f(integral_constant R) for a plan's radix r <= MAX (the same for the whole workgroup)
+template <int MAX = 16, typename F>
 __device__ __forceinline__ void gen_radix(int r, F&& f) {
   switch (r) {
     case 2: f(std::integral_constant<int, 2>{}); break;
@@ -262,9 +214,18 @@ __device__ __forceinline__ void gen_radix(int r, F&& f) {
     case 8: f(std::integral_constant<int, 8>{}); break;
     case 9: f(std::integral_constant<int, 9>{}); break;
     case 10: f(std::integral_constant<int, 10>{}); break;
-    case 12: f(std::integral_constant<int, 12>{}); break;
-    case 15: f(std::integral_constant<int, 15>{}); break;
-    default: f(std::integral_constant<int, 16>{}); break;
+    default:
+      if constexpr (MAX >= 16) {
+        if (r == 15) {
+          f(std::integral_constant<int, 15>{});
+          break;
+        } else if (r == 16) {
+          f(std::integral_constant<int, 16>{});
+          break;
+        }
+      }
+      f(std::integral_constant<int, 12>{});
+      break;
   }
 }
 
@@ -298,9 +259,9 @@ __device__ __forceinline__ void gen_each(int tid, const GPass& p, int rb, F&& f)
 template <int R, int EPT, int T>
 __device__ __forceinline__ void gen_read(int tid, float2* v, const float2* buf, int stride, const GPass& p, int rb) {
   gen_each<R, EPT, T>(tid, p, rb, [&](int b, int row, int j) {
-    const float2* in = buf + row * stride;
+    const float2* in = buf + row * stride + j + gdiv(j, p.mns) * p.rp;
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[b * R + q] = in[gpad(j + q * p.m)];
+    for (int q = 0; q < R; ++q) v[b * R + q] = in[q * p.rq];
   });
 }
 
@@ -321,18 +282,17 @@ __device__ __forceinline__ void gen_compute(int tid, float2* v, const float2* tw
 template <int R, int EPT, int T>
 __device__ __forceinline__ void gen_write(int tid, const float2* v, float2* buf, int stride, const GPass& p, int rb) {
   gen_each<R, EPT, T>(tid, p, rb, [&](int b, int row, int j) {
-    float2* out = buf + row * stride;
-    const int hi = gdiv(j, p.mns);
-    const int base = hi * p.ns * (R - 1) + j;  // (j div ns) ns R + j mod ns
+    // element (j div ns) ns R + j mod ns + q ns
+    float2* out = buf + row * stride + j + gdiv(j, p.mns) * (p.ns * (R - 1) + p.wp);
 #pragma unroll
-    for (int q = 0; q < R; ++q) out[gpad(base + q * p.ns)] = v[b * R + q];
+    for (int q = 0; q < R; ++q) out[q * p.ns] = v[b * R + q];
   });
 }
 
 // A whole pass in place (TW: not the first), ending with a barrier; the caller has a barrier before it.
 template <int EPT, int T, bool TW>
 __device__ __forceinline__ void gen_pass(float2* buf, int stride, const float2* tw, const GPass& p, int rb) {
-  gen_radix(p.r, [&](auto rc) {
+  gen_radix<EPT >= 16 ? 16 : 12>(p.r, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
     const int tid = gen_tid();
     float2 v[R * gen_per_thread(R, EPT)];
