@@ -296,6 +296,14 @@ int ssb_reconstruct_com(const int32_t* d_idx, const int64_t* d_off, int64_t fram
                         size_t state_bytes, float* d_phase, float* d_T, double* d_com64,
                         float* d_com32, int32_t* d_counts, int32_t* d_status, void* stream);
 
+/* The forward of a fit: ssb_reconstruct in mode FINALIZE or REFOCUS on accumulated events, for an
+ * ssb_backward that follows.  Same results to FP32 rounding; at scan lengths other than powers of two
+ * in [32, 1024] it uses the adjoint's transforms, whose rounding the FP64 gradient dL/dc carries, so that a
+ * fit's gradients do not depend on faster transforms of the other modes.  STEM_EINVAL for another mode. */
+int ssb_fit_forward(const stem_det* det, const stem_scan* scan, const stem_optics* optics, const stem_ssb* ssb,
+                    int mode, const float* d_theta, void* state, size_t state_bytes, float* d_phase,
+                    int32_t* d_status, void* stream);
+
 /* Regions of the state buffer a caller may read after the calls that fill them.
  *  STEM_REGION_D     binned counts D[kd][ry][rx], uint8 or uint16 (d_bits), after ACCUMULATE.
  *  STEM_REGION_X     complex64 [kd][mx][ry], mx in [0, Nx/2]: STEM_G_STORE, after ACCUMULATE, the

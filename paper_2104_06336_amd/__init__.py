@@ -355,6 +355,15 @@ class SsbState:
                                 self.state, com64=com64, com32=com32, counts=counts, theta=theta, phase=phase,
                                 T=T, d_status=self.status, stream=stream)
 
+    def _fit_forward(self, c, theta, phase):
+        """The phase for an adjoint that follows: refocus once a fit has finalized the state, else finalize."""
+        _dev(theta, torch.float32, "theta")
+        mode = STEM_SSB_REFOCUS if getattr(self, "_finalized", False) else STEM_SSB_FINALIZE
+        rc = lib().ssb_fit_forward(ctypes.byref(self.det), ctypes.byref(self.scan), ctypes.byref(self.optics_with(c)),
+                                   ctypes.byref(self.ssb), mode, _p(theta), _p(self.state), self.state.numel(),
+                                   _p(phase), _p(self.status), _stream(None))
+        _check(rc, "ssb_fit_forward")
+
     def g_panel(self, qs, stream=None) -> torch.Tensor:
         """G at the scan frequencies qs = [(my, mx), ...] as binned detector images
         (complex64 [len(qs), H/bin, W/bin]); call after finalize, oneshot or refocus."""
@@ -382,7 +391,7 @@ class SSBPhase(torch.autograd.Function):
         cv = [float(v) for v in c.detach().cpu().tolist()]
         th = theta.detach().contiguous() if theta is not None else None
         phase = torch.empty(st.scan.ny, st.scan.nx, dtype=torch.float32, device=st.state.device)
-        st.refocus(cv, th, phase=phase) if getattr(st, "_finalized", False) else st.finalize(cv, th, phase=phase)
+        st._fit_forward(cv, th, phase)
         st._finalized = st.ssb.g_mode == STEM_G_STORE
         ctx.st, ctx.cv, ctx.th = st, cv, th
         ctx.c_dtype, ctx.c_device = c.dtype, c.device

@@ -86,6 +86,9 @@ _SIGS = {
                                            ctypes.POINTER(Ssb), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p,
                                            ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
+    "ssb_fit_forward": (ctypes.c_int, [ctypes.POINTER(Det), ctypes.POINTER(Scan), ctypes.POINTER(Optics),
+                                       ctypes.POINTER(Ssb), ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p,
+                                       ctypes.c_size_t, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "ssb_state_region": (ctypes.c_int, [ctypes.POINTER(Det), ctypes.POINTER(Scan), ctypes.POINTER(Optics),
                                         ctypes.POINTER(Ssb), ctypes.c_int, ctypes.POINTER(ctypes.c_size_t),
                                         ctypes.POINTER(ctypes.c_size_t)]),

@@ -9,6 +9,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "common.h"
 #include "fft_generic.h"
@@ -249,7 +250,8 @@ static void launch_n(bool inv, const RowFftArgs& a, int in, int out, hipStream_t
 // loads RB rows into LDS (the input modes of k_row_fft), transforms them and writes them (its output
 // modes), grid-stride over batches of rows, its twiddles filled once.  Transposed outputs are written
 // rows-fastest (runs of RB consecutive rows per frequency).  RB is what LDS holds of 4096 elements,
-// less where that would leave compute units without a workgroup (1000 rows of 1000: 3 rows each).
+// less where that would leave compute units without a workgroup (1000 rows of 1000: 3 rows each; one row
+// each takes 16 against 19 us, but 35 against 33 us where partials are summed).
 
 constexpr int kGenRadices[11] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16};
 
@@ -366,14 +368,15 @@ bool scan_length_ok(int n) {
 
 constexpr int kGenEpt = 30;  // registers (complex) of a thread of the row passes: 4096 elements in any plan
 
-__global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p, int rb, int inv, int in_mode,
-                                                          int out_mode) {
+// SEG: IN_C64_SUM over segments (a.part_seg)
+template <int IN, bool SEG>
+__global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p, int rb, int inv, int out_mode) {
   extern __shared__ __align__(16) float2 s_g[];  // twiddles, then rb rows
   const int n = p.n, stride = p.len;
   float2* tw = s_g;
   float2* buf = s_g + gen_tw_size(p);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (in_mode == IN_C64_SUM && a.stats && blockIdx.x == 0) {
+  if (IN == IN_C64_SUM && a.stats && blockIdx.x == 0) {
     // the fused sums' per-wave counters: pair count below bit 40, 8-byte loads above
     __shared__ unsigned long long s_red[2][kGenThreads / 64];
     unsigned long long c = 0, l = 0;
@@ -407,43 +410,81 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
   gen_twiddles(tw, (double2*)buf, p);
   const int64_t nbatch = (a.nrows + rb - 1) / rb;
   const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM;
-  const int nh = n / 2 + 1;
   const uint32_t mrb = rb == 1 ? 0u : (uint32_t)((0x100000000ull + rb - 1) / rb);
   for (int64_t bt = blockIdx.x; bt < nbatch; bt += gridDim.x) {
     const int64_t r0 = bt * rb;
-    for (int e = threadIdx.x; e < rb * n; e += kGenThreads) {
-      const int rl = gdiv(e, p.mn), i = e - rl * n;
-      const int64_t r = r0 + rl;
-      float2 x = make_float2(0.f, 0.f);
-      if (r < a.nrows) {
-        const int64_t el = r * n + i;
-        if (in_mode == IN_C64) {
-          x = a.in_c[el];
-        } else if (in_mode == IN_C64_SUM) {
-          if (a.part_seg) {
-            const int64_t q0 = min(max(a.part_seg[r], (int64_t)0), a.part_seg_rows);
-            const int64_t q1 = min(max(a.part_seg[r + 1], q0), a.part_seg_rows);
-            for (int64_t q = q0; q < q1; ++q) x = cadd(x, a.in_c[q * n + i]);
-          } else {
-            for (int q = 0; q < a.nparts; ++q) x = cadd(x, a.in_c[(int64_t)q * a.part_stride + el]);
+    // eight elements' loads in flight per thread (past the last element or row an in-range one is
+    // loaded again)
+    constexpr int U = 8;
+    for (int e0 = threadIdx.x; e0 < rb * n; e0 += U * kGenThreads) {
+      int64_t el[U];
+      int pos[U];
+      float2 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = min(e0 + u * kGenThreads, rb * n - 1);
+        const int rl = gdiv(e, p.mn), i = e - rl * n;
+        el[u] = min(r0 + rl, a.nrows - 1) * n + i;
+        pos[u] = rl * stride + i;
+      }
+      if constexpr (IN == IN_C64) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = a.in_c[el[u]];
+      } else if constexpr (IN == IN_F32_PAIR) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          x[u] = make_float2(a.in_f0[el[u]] * a.s0, a.in_f1 ? a.in_f1[el[u]] * a.s1 : 0.f);
+      } else if constexpr (IN == IN_F64_PAIR) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          x[u] = make_float2((float)(a.in_d0[el[u]] * (double)a.s0),
+                             a.in_d1 ? (float)(a.in_d1[el[u]] * (double)a.s1) : 0.f);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = make_float2(0.f, 0.f);
+        if constexpr (SEG) {
+          int64_t q0[U];
+          int qn[U], most = 0;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int64_t r = min(r0 + gdiv(min(e0 + u * kGenThreads, rb * n - 1), p.mn), a.nrows - 1);
+            const int64_t s0 = min(max(a.part_seg[r], (int64_t)0), a.part_seg_rows);
+            qn[u] = (int)(min(max(a.part_seg[r + 1], s0), a.part_seg_rows) - s0);
+            q0[u] = s0 * n + (el[u] - r * n);
+            most = max(most, qn[u]);
           }
-          if (a.norm_cnt) {
-            const int32_t cnt = a.norm_cnt[el];
-            x = cnt > 0 ? make_float2(x.x / (float)cnt, x.y / (float)cnt) : make_float2(0.f, 0.f);
-          }
-          if (a.sum_out) a.sum_out[el] = x;
-        } else if (in_mode == IN_HALF_C64) {
-          const float2* hr = a.in_c + r * nh;
-          x = 2 * i <= n ? hr[i] : cconj(hr[n - i]);
-        } else if (in_mode == IN_F32_PAIR) {
-          x.x = a.in_f0[el] * a.s0;
-          x.y = a.in_f1 ? a.in_f1[el] * a.s1 : 0.f;
+          for (int q = 0; q < most; ++q)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (q < qn[u]) x[u] = cadd(x[u], a.in_c[q0[u] + (int64_t)q * n]);
         } else {
-          x.x = (float)(a.in_d0[el] * (double)a.s0);
-          x.y = a.in_d1 ? (float)(a.in_d1[el] * (double)a.s1) : 0.f;
+          // four partials' loads together, added in order
+          for (int q = 0; q < a.nparts; q += 4) {
+            float2 t[4][U];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const float2* src = a.in_c + min(q + k, a.nparts - 1) * a.part_stride;
+#pragma unroll
+              for (int u = 0; u < U; ++u) t[k][u] = src[el[u]];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                if (q + k < a.nparts) x[u] = cadd(x[u], t[k][u]);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (a.norm_cnt) {
+            const int32_t cnt = a.norm_cnt[el[u]];
+            x[u] = cnt > 0 ? make_float2(x[u].x / (float)cnt, x[u].y / (float)cnt) : make_float2(0.f, 0.f);
+          }
+          if (a.sum_out) a.sum_out[el[u]] = x[u];  // an element loaded again is stored again, the same
         }
       }
-      buf[rl * stride + i] = inv ? cconj(x) : x;
+#pragma unroll
+      for (int u = 0; u < U; ++u) buf[pos[u]] = inv ? cconj(x[u]) : x[u];
     }
     __syncthreads();
     gen_pass<kGenEpt, kGenThreads, false>(buf, stride, tw, p.p[0], rb);
@@ -479,10 +520,21 @@ static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFf
   if (rb < 1) rb = 1;
   const int64_t batches = (a.nrows + rb - 1) / rb;
   const size_t lds = gen_lds(p, (int)rb, p.len);
-  const int res = resident_blocks((const void*)k_grow_fft, kGenThreads, lds);
-  const int64_t cap = res > 0 ? res : 1024;
-  hipLaunchKernelGGL(k_grow_fft, dim3((unsigned)(batches < cap ? batches : cap)), dim3(kGenThreads), lds, stream, a,
-                     p, (int)rb, inverse ? 1 : 0, (int)in, (int)out);
+  auto go = [&](auto mode, auto seg) {
+    const auto fn = k_grow_fft<decltype(mode)::value, decltype(seg)::value>;
+    const int res = resident_blocks((const void*)fn, kGenThreads, lds);
+    const int64_t cap = res > 0 ? res : 1024;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(batches < cap ? batches : cap)), dim3(kGenThreads), lds, stream, a, p,
+                       (int)rb, inverse ? 1 : 0, (int)out);
+  };
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  if (in == IN_C64) go(std::integral_constant<int, IN_C64>{}, F_{});
+  else if (in == IN_F32_PAIR) go(std::integral_constant<int, IN_F32_PAIR>{}, F_{});
+  else if (in == IN_F64_PAIR) go(std::integral_constant<int, IN_F64_PAIR>{}, F_{});
+  else if (in != IN_C64_SUM) return STEM_EINVAL;
+  else if (a.part_seg) go(std::integral_constant<int, IN_C64_SUM>{}, T_{});
+  else go(std::integral_constant<int, IN_C64_SUM>{}, F_{});
   STEM_LAUNCH_CHECK();
   return STEM_OK;
 }
@@ -600,6 +652,7 @@ int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2
 int launch_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream) {
   if (a.nrows <= 0) return STEM_OK;
   STEM_TRACE(a.tag ? a.tag : "row_fft", stream);
+  if (in == IN_U8 || in == IN_U16 || out == OUT_X) return STEM_EINVAL;
   if (!fast_length(n)) return launch_generic(n, inverse, in, out, a, stream);
   switch (n) {
     case 32: launch_n<32>(inverse, a, in, out, stream); break;
@@ -610,6 +663,81 @@ int launch_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& 
     case 1024: launch_n<1024>(inverse, a, in, out, stream); break;
     default: return STEM_EINVAL;
   }
+  STEM_LAUNCH_CHECK();
+  return STEM_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
+// The summed input of an IN_C64_SUM pass by itself, for many partials: one element per lane, its
+// partials added in order (as the pass adds them, bit for bit) with kPartLoads of them in flight.  In the
+// pass itself a wave adds the partials of 16 elements per lane, and a short transform leaves only a
+// few waves to do so: 64 x 64 (one workgroup, 176 partials) 86 us, 256 x 256 (33) 44 us, 512 x 512 (10
+// segments) 24 us, against 9 to 10 us here and 6 to 9 us for the pass without them.
+
+constexpr int kPartLoads = 16;
+
+template <bool SEG>
+__global__ void __launch_bounds__(64) k_part_sum(RowFftArgs a, int n) {
+  const int lane = threadIdx.x;
+  if (a.stats && blockIdx.x == gridDim.x - 1) {
+    // the last workgroup, which no element has, adds the fused sums' per-wave counters
+    unsigned long long c = 0, l = 0;
+    for (int64_t i0 = lane; i0 < a.nwcnt; i0 += 64 * kPartLoads) {
+      unsigned long long w[kPartLoads];
+#pragma unroll
+      for (int u = 0; u < kPartLoads; ++u) w[u] = i0 + 64 * u < a.nwcnt ? a.wcnt[i0 + 64 * u] : 0ull;
+#pragma unroll
+      for (int u = 0; u < kPartLoads; ++u) {
+        c += w[u] & ((1ull << 40) - 1);
+        l += w[u] >> 40;
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      c += __shfl_xor(c, off);
+      l += __shfl_xor(l, off);
+    }
+    if (lane == 0) {
+      a.stats[0] = c;
+      a.stats[1] = SEG ? (unsigned long long)a.part_seg[a.nrows] : (unsigned long long)a.stats_groups;
+      a.stats[2] = 8ull * l;
+      a.stats[3] = (unsigned long long)a.stats_chunks;
+      if (a.ready_out) *a.ready_out = a.ready_val;
+    }
+    return;
+  }
+  const int64_t el = (int64_t)blockIdx.x * 64 + lane, total = a.nrows * n;
+  if (el >= total) return;
+  const float2* src = a.in_c + el;
+  int64_t step = a.part_stride;
+  int count = a.nparts;
+  if constexpr (SEG) {
+    const int64_t r = el / n;
+    const int64_t s0 = min(max(a.part_seg[r], (int64_t)0), a.part_seg_rows);
+    count = (int)(min(max(a.part_seg[r + 1], s0), a.part_seg_rows) - s0);
+    src = a.in_c + s0 * n + (el - r * n);
+    step = n;
+  }
+  float2 x = make_float2(0.f, 0.f);
+  for (int q = 0; q < count; q += kPartLoads) {
+    float2 t[kPartLoads];
+#pragma unroll
+    for (int u = 0; u < kPartLoads; ++u) t[u] = q + u < count ? src[(q + u) * step] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < kPartLoads; ++u) x = cadd(x, t[u]);
+  }
+  if (a.norm_cnt) {
+    const int32_t c = a.norm_cnt[el];
+    x = c > 0 ? make_float2(x.x / (float)c, x.y / (float)c) : make_float2(0.f, 0.f);
+  }
+  a.sum_out[el] = x;
+}
+
+int launch_part_sum(int n, const RowFftArgs& a, hipStream_t stream) {
+  if (!a.sum_out || a.nrows <= 0) return STEM_EINVAL;
+  STEM_TRACE("part_sum", stream);
+  const dim3 grid((unsigned)((a.nrows * n + 63) / 64 + (a.stats ? 1 : 0))), blk(64);
+  if (a.part_seg) hipLaunchKernelGGL(k_part_sum<true>, grid, blk, 0, stream, a, n);
+  else hipLaunchKernelGGL(k_part_sum<false>, grid, blk, 0, stream, a, n);
   STEM_LAUNCH_CHECK();
   return STEM_OK;
 }

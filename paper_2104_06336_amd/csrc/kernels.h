@@ -34,8 +34,8 @@ int launch_bin(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
 bool bin_builds_sets(const stem_det& det, double r2);
 
 // ---- fft2.hip: batched row FFTs of length n (power of two, 32..1024) --------------------------
-enum RowIn { IN_C64 = 0, IN_C64_SUM = 1, IN_F32_PAIR = 2, IN_F64_PAIR = 3, IN_HALF_C64 = 4 };
-enum RowOut { OUT_T_C64 = 0, OUT_ROW_C64 = 1, OUT_ROW_RE = 2, OUT_ROW_IM = 3, OUT_T_RE = 4, OUT_T_IM = 5 };
+enum RowIn { IN_C64 = 0, IN_C64_SUM = 1, IN_F32_PAIR = 2, IN_F64_PAIR = 3, IN_HALF_C64 = 4, IN_U8 = 5, IN_U16 = 6 };
+enum RowOut { OUT_T_C64 = 0, OUT_ROW_C64 = 1, OUT_ROW_RE = 2, OUT_ROW_IM = 3, OUT_T_RE = 4, OUT_T_IM = 5, OUT_X = 6 };
 
 struct RowFftArgs {
   int64_t nrows;
@@ -52,9 +52,13 @@ struct RowFftArgs {
   const float* in_f1;
   const double* in_d0;     // IN_F64_PAIR
   const double* in_d1;
+  const void* in_u;        // IN_U8 / IN_U16 (launch_fit_row_fft only): real row r at in_u + r*n
   float s0, s1;
   // outputs
   float2* out_c;           // OUT_T_*: element (r, m) at out[m*out_stride + r]; OUT_ROW_*: out[r*n + m];
+                           // OUT_X (launch_fit_row_fft only): m <= n/2 of row r = kd*xrows + y at
+                           // out[(kd*(n/2+1) + m)*xrows + y]
+  int32_t xrows;
   float* out_f;
   int64_t out_stride;
   float2 osc;              // complex factor applied to every output value
@@ -75,6 +79,11 @@ struct RowFftArgs {
 };
 
 int launch_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream);
+// the same in the arithmetic a fit keeps at the other lengths (fft_fit.hip); also real rows of counts
+int launch_fit_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream);
+// a's summed input (IN_C64_SUM: partials, segments, normalisation, counters) stored at a.sum_out, for a
+// pass that then reads it with IN_C64
+int launch_part_sum(int n, const RowFftArgs& a, hipStream_t stream);
 // row transform of nrows = pixels * ny real rows of n counts (d_bits 8 or 16) at any length the
 // library transforms: row kd*ny + y to X[(kd*(n/2+1) + m)*ny + y], m <= n/2
 int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2* X, hipStream_t stream);

@@ -37,9 +37,11 @@ struct SsbLayout {
   int64_t F;
   bool store;     // STEM_G_STORE
   int xpix;       // pixels whose row-transformed columns the X region holds (n_k, or one chunk)
+  int ypix;       // pixels of a fit's column-transform scratch (stored G of the other lengths), or 0
   int nchunks;    // pixel chunks of a sum
+  int fchunks;    // and of a fit's sum at the other lengths
   int64_t pcap;   // entries of the pruned G array (0 without STEM_G_STORE)
-  size_t rows, kc, kchi, cst, cmask, lut, stats, npq, D, X, poff, ptot, pg, T, A, Tb, pdc, pdth, part, wcnt, pws, pcs,
+  size_t rows, kc, kchi, cst, cmask, lut, stats, npq, D, X, Y, poff, ptot, pg, T, A, Tb, pdc, pdth, part, wcnt, pws, pcs,
       total;
   int nmw;      // 64-bit words per column set of the active-pixel mask
   int groups;   // pixel groups of the fused column sum (the same for every chunk)
@@ -47,6 +49,7 @@ struct SsbLayout {
   int ncs;      // column sets (colset_width(Ny) half-spectrum columns each)
   bool fast;    // both scan lengths taken by the fused kernels (powers of two in [32, 1024])
   int64_t nwy;  // waves of the fused column sum (and, for the fast lengths, of the fused adjoint)
+  int64_t nwp;  // waves of a fit's sum over the full columns of G (other scan lengths)
   int64_t nws;  // pieces the refocus sum over the stored values aims at
   int64_t nwq;  // STEM_G_STORE: waves (at most) of the refocus sum over the stored values
   int64_t part_rows;  // rows of Ny values the partial-sum buffer holds
@@ -109,12 +112,15 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     nc = nc < 1 ? 1 : nc > n_k ? n_k : nc;
     L->nchunks = (n_k + nc - 1) / nc;
     chunk = (n_k + L->nchunks - 1) / L->nchunks;
+    L->fchunks = L->nchunks;
   }
+  L->ypix = 0;
   if (L->store) {
     // every pixel's row transform (it also serves the panel of G), summed in one go; the other
     // lengths take the pixels in chunks of a scratch size the caller sets
     L->xpix = n_k;
     if (L->fast || ssb.scratch_mib == 0) L->nchunks = 1;
+    if (!L->fast) L->ypix = chunk;
     L->pcap = pruned_bound(scan, op, n_k);
   } else {
     L->xpix = chunk;
@@ -137,6 +143,7 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
   L->npq = o;   o = align256(o + sizeof(int32_t) * (size_t)L->F);
   L->D = o;     o = align256(o + (size_t)n_k * L->F * (ssb.d_bits / 8));
   L->X = o;     o = align256(o + (size_t)L->xpix * per_pixel);
+  L->Y = o;     o = align256(o + (size_t)L->ypix * per_pixel);
   L->poff = o;  o = align256(o + (L->store ? sizeof(int64_t) * ((size_t)n_k * scan.nx + 1) : 0));
   L->ptot = o;  o = align256(o + (L->store ? sizeof(int64_t) * (size_t)scan.nx : 0));
   L->pg = o;    o = align256(o + sizeof(float2) * (size_t)L->pcap);
@@ -159,6 +166,7 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     pg = pg > n_k ? n_k : pg;
     pg = pg > gmax ? gmax : pg;
     L->pgroups = pg < 1 ? 1 : pg;
+    L->nwp = psum_launch_waves(scan.ny, scan.nx, L->pgroups);
     L->nwa = padj_partials(scan.nx, L->pgroups);
     // the balanced pieces: as many as the GPU holds waves at once (more, one per column with
     // pairs, when the columns outnumber them)
@@ -168,6 +176,7 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     L->nwq = L->store ? ((nws > scan.nx ? nws : scan.nx) + w - 1) / w * w : 0;
   }
   int64_t nw = L->nwy > L->nwq ? L->nwy : L->nwq;
+  nw = nw > L->nwp ? nw : L->nwp;
   nw = nw > L->nwa ? nw : L->nwa;
   const int rows = L->ncs > scan.nx ? L->ncs : scan.nx;
   const int parts = L->groups > L->pgroups ? L->groups : L->pgroups;
@@ -532,6 +541,7 @@ struct Bufs {
   int32_t* npq;
   void* D;
   float2* X;
+  float2* Y;
   int64_t* poff;
   int64_t* ptot;
   float2* pg;
@@ -556,7 +566,7 @@ static Bufs carve(void* state, const SsbLayout& L) {
   char* p = (char*)state;
   return Bufs{(RowRun*)(p + L.rows), (double2*)(p + L.kc), (double*)(p + L.kchi), (int4*)(p + L.cst),
               (uint64_t*)(p + L.cmask), (int16_t*)(p + L.lut), (unsigned long long*)(p + L.stats),
-              (int32_t*)(p + L.npq), (void*)(p + L.D), (float2*)(p + L.X), (int64_t*)(p + L.poff),
+              (int32_t*)(p + L.npq), (void*)(p + L.D), (float2*)(p + L.X), (float2*)(p + L.Y), (int64_t*)(p + L.poff),
               (int64_t*)(p + L.ptot), (float2*)(p + L.pg), (float2*)(p + L.T), (float2*)(p + L.A), (float2*)(p + L.Tb),
               (double*)(p + L.pdc), (float*)(p + L.pdth), (float2*)(p + L.part),
               (unsigned long long*)(p + L.wcnt), (PieceTab*)(p + L.pws), (int64_t*)(p + L.pcs)};
@@ -616,10 +626,10 @@ static void need_finalize(YArgs& a, const SsbLayout& L, const Bufs& b, int32_t* 
   a.status = d_status;
 }
 
-// pixels [k0, k1) of chunk ch
-static void chunk_range(const SsbLayout& L, int ch, int& k0, int& k1) {
-  k0 = (int)((int64_t)L.n_k * ch / L.nchunks);
-  k1 = (int)((int64_t)L.n_k * (ch + 1) / L.nchunks);
+// pixels [k0, k1) of chunk ch of nchunks
+static void chunk_range(const SsbLayout& L, int nchunks, int ch, int& k0, int& k1) {
+  k0 = (int)((int64_t)L.n_k * ch / nchunks);
+  k1 = (int)((int64_t)L.n_k * (ch + 1) / nchunks);
 }
 
 // row transform of the pixels [k0, k1) (all scan rows) into the X region
@@ -633,22 +643,35 @@ static int xstage_pixels(const SsbLayout& L, const Bufs& b, const stem_ssb& ssb,
                                    s);
 }
 
-// The other scan lengths: row transform of the pixels [k0, k1) (all rows) into x, and (for the
-// adjoint) the column transforms of those pixels in place.
+// The other scan lengths: row transform of the pixels [k0, k1) (all rows) into x.
 static int xstage_generic(const SsbLayout& L, const Bufs& b, const stem_ssb& ssb, int ny, int nx, int k0, int k1,
                           float2* x, hipStream_t s) {
   return launch_gen_x(nx, (const uint8_t*)b.D + (size_t)k0 * L.F * (ssb.d_bits / 8), ssb.d_bits, ny,
                       (int64_t)(k1 - k0) * ny, x, s);
 }
 
-static int colfft_generic(const SsbLayout& L, int ny, int k0, int k1, float2* x, hipStream_t s) {
+// The same for a fit (one real row per transform), and its column transforms of those pixels from src into dst
+// (in place when equal).
+static int xstage_fit(const SsbLayout& L, const Bufs& b, const stem_ssb& ssb, int ny, int nx, int k0, int k1,
+                      hipStream_t s) {
+  RowFftArgs a{};
+  a.nrows = (int64_t)(k1 - k0) * ny;
+  a.in_u = (const uint8_t*)b.D + (size_t)k0 * L.F * (ssb.d_bits / 8);
+  a.out_c = b.X;
+  a.xrows = ny;
+  a.osc = make_float2(1.f, 0.f);
+  a.tag = "xstage_fft";
+  return launch_fit_row_fft(nx, false, ssb.d_bits == 8 ? IN_U8 : IN_U16, OUT_X, a, s);
+}
+
+static int colfft_fit(const SsbLayout& L, int ny, int k0, int k1, const float2* src, float2* dst, hipStream_t s) {
   RowFftArgs a{};
   a.nrows = (int64_t)(k1 - k0) * L.nh;
-  a.in_c = x;
-  a.out_c = x;
+  a.in_c = src;
+  a.out_c = dst;
   a.osc = make_float2(1.f, 0.f);
   a.tag = "ystage_fft";
-  return launch_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s);
+  return launch_fit_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s);
 }
 
 // T = sum of the partial sums (column-major [mx][my]), divided by the pair count of each Q when
@@ -657,10 +680,12 @@ static int colfft_generic(const SsbLayout& L, int ny, int k0, int k1, float2* x,
 // part_seg: the partials are the rows of the refocus sum's pieces (row mx of T adds rows
 // part_seg[mx] .. part_seg[mx + 1] - 1 of b.part) instead of nparts planes
 // mark: the call is a FINALIZE, and the first pass leaves ready_tag in the state's mark word
+// fit: by the transforms of a fit
 static int run_phase(const SsbLayout& L, const Bufs& b, const stem_scan& sc, int nparts, int64_t nwaves, int nchunks,
-                     const int32_t* npq, float* d_phase, float* d_T, hipStream_t s, bool mark,
+                     const int32_t* npq, float* d_phase, float* d_T, hipStream_t s, bool mark, bool fit,
                      const int64_t* part_seg = nullptr) {
   const int ny = sc.ny, nx = sc.nx;
+  const auto row_fft = fit ? launch_fit_row_fft : launch_row_fft;
   RowFftArgs a{};
   // inverse along my of each mx row of T -> A[ry][mx]; the summed T is kept in the state
   a.nrows = nx;
@@ -682,8 +707,17 @@ static int run_phase(const SsbLayout& L, const Bufs& b, const stem_scan& sc, int
   a.stats_chunks = nchunks;
   a.ready_out = mark ? b.stats + 4 : nullptr;
   a.ready_val = ready_tag(L);
-  int st = launch_row_fft(ny, true, IN_C64_SUM, OUT_T_C64, a, s);
-  if (st) return st;
+  // more than eight partials (on average, in segments) are added by a kernel of their own: the pass that
+  // adds them itself took 24 us at 512 x 512 (10 segments) and 44 us at 256 x 256 (33 planes), but it is
+  // one launch less at 1024 x 1024 (5 planes, 4 segments)
+  RowIn in = IN_C64_SUM;
+  int st;
+  if ((part_seg ? nwaves / nx : nparts) > 8) {
+    if ((st = launch_part_sum(ny, a, s))) return st;
+    a.in_c = b.T;
+    in = IN_C64;
+  }
+  if ((st = row_fft(ny, true, in, OUT_T_C64, a, s))) return st;
   if (d_phase) {
     a = RowFftArgs{};
     a.nrows = ny;
@@ -691,7 +725,7 @@ static int run_phase(const SsbLayout& L, const Bufs& b, const stem_scan& sc, int
     a.out_f = d_phase;
     a.osc = make_float2((float)(1.0 / (double)L.F), 0.f);
     a.tag = "phase_fft";
-    if ((st = launch_row_fft(nx, true, IN_C64, OUT_ROW_IM, a, s))) return st;
+    if ((st = row_fft(nx, true, IN_C64, OUT_ROW_IM, a, s))) return st;
   }
   if (d_T) {
     STEM_TRACE("t_transpose", s);
@@ -779,10 +813,11 @@ extern "C" int ssb_state_region(const stem_det* det, const stem_scan* scan, cons
   return STEM_OK;
 }
 
+// fit: the sum precedes an ssb_backward, whose arithmetic it keeps at the other scan lengths
 static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame0, int64_t n_frames,
                        const stem_det* det, const stem_scan* scan, const stem_optics* optics, const stem_ssb* ssb,
                        int mode, const float* d_theta, void* state, size_t state_bytes, float* d_phase, float* d_T,
-                       const ComOut* com, int32_t* d_status, void* stream_) {
+                       const ComOut* com, int32_t* d_status, void* stream_, bool fit = false) {
   int n_k;
   int st = check_common(det, scan, optics, ssb, &n_k);
   if (st) return st;
@@ -842,14 +877,40 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
     a.theta = d_theta;
     if ((st = launch_psum_stream(ny, a, o, chi0, (int)L.nwq, b.pws, b.pcs, s))) return st;
     return run_phase(L, b, *scan, L.pgroups, L.nwq, 1, ssb->normalize ? b.npq : nullptr, d_phase, d_T, s, false,
-                     b.pcs);
+                     fit, b.pcs);
+  } else if (!L.fast && fit) {
+    // row and column transforms, then Eq. 3 per (pixel, column) run over the full columns of G, chunk
+    // by chunk
+    a.ngroups = L.pgroups;
+    if (L.store) {
+      if ((st = xstage_fit(L, b, *ssb, ny, nx, 0, n_k, s))) return st;
+      if ((st = run_prune_offsets(L, b, nx, d_status, s))) return st;
+    }
+    for (int ch = 0; ch < L.fchunks; ++ch) {
+      int k0, k1;
+      chunk_range(L, L.fchunks, ch, k0, k1);
+      if (L.store) {
+        if ((st = colfft_fit(L, ny, k0, k1, b.X + (size_t)k0 * L.nh * ny, b.Y, s))) return st;
+        a.X = b.Y;
+      } else {
+        if ((st = xstage_fit(L, b, *ssb, ny, nx, k0, k1, s))) return st;
+        if ((st = colfft_fit(L, ny, k0, k1, b.X, b.X, s))) return st;
+      }
+      a.xk0 = k0;
+      a.k0 = k0;
+      a.k1 = k1;
+      a.accumulate = ch > 0;
+      if ((st = launch_psum(ny, a, o, chi0, L.store, s))) return st;
+    }
+    return run_phase(L, b, *scan, L.pgroups, L.nwp, L.fchunks, ssb->normalize ? b.npq : nullptr, d_phase, d_T, s,
+                     !refocus, true);
   } else if (!L.fast) {
     // the other scan lengths: row transforms, then the column transforms fused with Eq. 3, chunk by
     // chunk
     if (L.store && (st = run_prune_offsets(L, b, nx, d_status, s))) return st;
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
-      chunk_range(L, ch, k0, k1);
+      chunk_range(L, L.nchunks, ch, k0, k1);
       // STEM_G_STORE keeps every pixel's columns, the other mode one chunk's
       float2* x = L.store ? b.X + (size_t)k0 * L.nh * ny : b.X;
       if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, x, s))) return st;
@@ -867,7 +928,7 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
     // G recomputed chunk by chunk: row transform of the chunk's pixels, then the fused sum on it
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
-      chunk_range(L, ch, k0, k1);
+      chunk_range(L, L.nchunks, ch, k0, k1);
       if ((st = xstage_pixels(L, b, *ssb, ny, nx, k0, k1, s))) return st;
       a.xk0 = k0;
       a.k0 = k0;
@@ -877,7 +938,7 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
     }
   }
   return run_phase(L, b, *scan, L.groups, L.nwy, L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase,
-                   d_T, s, !refocus);
+                   d_T, s, !refocus, fit);
 }
 
 extern "C" int ssb_reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame0, int64_t n_frames,
@@ -901,6 +962,14 @@ extern "C" int ssb_reconstruct_com(const int32_t* d_idx, const int64_t* d_off, i
   const ComOut com{d_com64, d_com32, d_counts, (int64_t)scan->ny * scan->nx, det->cx, det->cy};
   return reconstruct(d_idx, d_off, frame0, n_frames, det, scan, optics, ssb, mode, d_theta, state, state_bytes,
                      d_phase, d_T, &com, d_status, stream_);
+}
+
+extern "C" int ssb_fit_forward(const stem_det* det, const stem_scan* scan, const stem_optics* optics,
+                               const stem_ssb* ssb, int mode, const float* d_theta, void* state, size_t state_bytes,
+                               float* d_phase, int32_t* d_status, void* stream_) {
+  if (mode != STEM_SSB_FINALIZE && mode != STEM_SSB_REFOCUS) return STEM_EINVAL;
+  return reconstruct(nullptr, nullptr, 0, 0, det, scan, optics, ssb, mode, d_theta, state, state_bytes, d_phase,
+                     nullptr, nullptr, d_status, stream_, true);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1164,14 +1233,14 @@ extern "C" int ssb_backward(const float* d_dLdphi, const stem_det* det, const st
   a.out_stride = ny;
   a.osc = make_float2(1.f, 0.f);
   a.tag = "adj_fft";
-  if ((st = launch_row_fft(nx, false, IN_F32_PAIR, OUT_T_C64, a, s))) return st;
+  if ((st = launch_fit_row_fft(nx, false, IN_F32_PAIR, OUT_T_C64, a, s))) return st;
   a = RowFftArgs{};
   a.nrows = nx;
   a.in_c = b.A;
   a.out_c = b.Tb;
   a.osc = make_float2(0.f, (float)(1.0 / (double)L.F));
   a.tag = "adj_fft";
-  if ((st = launch_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s))) return st;
+  if ((st = launch_fit_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s))) return st;
   // chi(Kc) + theta for these coefficients (evaluated per pixel by the adjoint over the stored
   // values); the interval table and mask are the last sum's
   if (!L.store && (st = run_chi_table(b, d_theta, n_k, o, s))) return st;
@@ -1190,9 +1259,9 @@ extern "C" int ssb_backward(const float* d_dLdphi, const stem_det* det, const st
     y.ngroups = L.pgroups;
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
-      chunk_range(L, ch, k0, k1);
-      if ((st = xstage_generic(L, b, *ssb, ny, nx, k0, k1, b.X, s))) return st;
-      if ((st = colfft_generic(L, ny, k0, k1, b.X, s))) return st;
+      chunk_range(L, L.nchunks, ch, k0, k1);
+      if ((st = xstage_fit(L, b, *ssb, ny, nx, k0, k1, s))) return st;
+      if ((st = colfft_fit(L, ny, k0, k1, b.X, b.X, s))) return st;
       y.xk0 = k0;
       y.k0 = k0;
       y.k1 = k1;
@@ -1204,7 +1273,7 @@ extern "C" int ssb_backward(const float* d_dLdphi, const stem_det* det, const st
   } else {
     for (int ch = 0; ch < L.nchunks; ++ch) {
       int k0, k1;
-      chunk_range(L, ch, k0, k1);
+      chunk_range(L, L.nchunks, ch, k0, k1);
       if ((st = xstage_pixels(L, b, *ssb, ny, nx, k0, k1, s))) return st;
       y.xk0 = k0;
       y.k0 = k0;

@@ -15,10 +15,11 @@
 // FINALIZE, k_stream_*).  A piece's partial T is one row of the partial buffer; the phase pass
 // adds a column's rows in order.
 //
-// The adjoint of the other scan lengths with G recomputed (k_padj, FULLG): the runs are read from a
-// block of full half-spectrum columns of G (pixel kd's column c at X + ((kd - xk0) (Nx/2+1) + c) Ny; a
-// column mx > Nx/2 is the conjugate of column Nx - mx at -my), chunk by chunk of pixels; a workgroup
-// owns a column and a pixel group.
+// A fit at the other scan lengths (k_psum, k_padj with FULLG): the runs are read from a block of full
+// half-spectrum columns of G (pixel kd's column c at X + ((kd - xk0) (Nx/2+1) + c) Ny; a column
+// mx > Nx/2 is the conjugate of column Nx - mx at -my), chunk by chunk of pixels; a wave (refocus)
+// or workgroup (adjoint) owns a column and a pixel group, its partial T going to part[g]
+// (column-major [mx][my]).  With PWRITE the values read are also stored as the pruned array.
 #pragma once
 
 #include "ssb_fused.h"
@@ -199,17 +200,20 @@ struct RoundCursor {
   __device__ __forceinline__ Round load_target(int nb) const { return at.j < nb ? at : safe; }
 };
 
-// A workgroup's work: column mx and the pixels [kd_a, kd_b) of group g = blk % ngroups of ngroups equal
-// shares of [k0, k1).
+// A wave's or workgroup's work: column mx and the pixels [kd_a, kd_b) of its group g.
 struct PrunedItem {
   int mx, g, kd_a, kd_b;
   bool live;
 };
 
-__device__ __forceinline__ PrunedItem pruned_item(const YArgs& a, int64_t blk) {
+// The work of wave w of workgroup blk: the pixels [kd_a, kd_b) of group g = blk % ngroups of
+// ngroups equal shares of [k0, k1), and column mx = (blk / ngroups) W + w (W = 1 for the adjoint,
+// whose workgroup takes one column).  In the column-major pruned array the runs of a column's
+// pixels follow one another, so each item reads one contiguous stretch.
+__device__ __forceinline__ PrunedItem pruned_item(const YArgs& a, int64_t blk, int w, int W) {
   PrunedItem it{0, 0, 0, 0, false};
   it.g = (int)(blk % a.ngroups);
-  it.mx = (int)(blk / a.ngroups);
+  it.mx = (int)(blk / a.ngroups) * W + w;
   if (it.mx >= a.nx) return it;
   it.kd_a = a.k0 + (int)((int64_t)(a.k1 - a.k0) * it.g / a.ngroups);
   it.kd_b = a.k0 + (int)((int64_t)(a.k1 - a.k0) * (it.g + 1) / a.ngroups);
@@ -234,7 +238,7 @@ __device__ __forceinline__ WavePixels wave_pixels(int kd_a, int kd_b, int w, int
 // skipped (a wave-uniform test); inside a slice every lane works, and the lanes past the run's end
 // read and write the wave's spare LDS slot t[ny], so the LDS accesses of a round issue back to back
 // with no divergent branch between them.  Returns the pairs added.
-template <bool CHI0>
+template <bool CHI0, bool FULLG, bool PWRITE>
 __device__ __forceinline__ unsigned long long sum_batch(const YArgs& a, const RunBatch& rb, int kb, int mx, int ny,
                                                         int lane, float2* t) {
   constexpr int D = kSumDepth;
@@ -249,7 +253,7 @@ __device__ __forceinline__ unsigned long long sum_batch(const YArgs& a, const Ru
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     const Round l = it.load_target(nb);
-    load_round<false>(a, rb.at(l.j), kb + l.j, mx, ny, l.u0, lane, buf[d]);
+    load_round<FULLG>(a, rb.at(l.j), kb + l.j, mx, ny, l.u0, lane, buf[d]);
     pos[d] = it.take(rb);
   }
   while (pos[0].j < nb) {
@@ -270,6 +274,9 @@ __device__ __forceinline__ unsigned long long sum_batch(const YArgs& a, const Ru
           ad[q] = u < r.len ? (iy < 0 ? iy + ny : iy) : ny;
           val[q] = buf[d][q];
           if (u0 + 64 * q < r.len) {
+            if constexpr (PWRITE) {
+              if (u < r.len && r.e0 + u < a.pcap) a.pgw[r.e0 + u] = val[q];
+            }
             if constexpr (!CHI0) {
               const float2 e = expi_rev(chi_row_eval(ch, (double)iy));
               const float2 x = val[q];
@@ -284,11 +291,44 @@ __device__ __forceinline__ unsigned long long sum_batch(const YArgs& a, const Ru
         for (int q = 0; q < 4; ++q) t[ad[q]] = cadd(tv[q], val[q]);
       }
       const Round l = it.load_target(nb);
-      load_round<false>(a, rb.at(l.j), kb + l.j, mx, ny, l.u0, lane, buf[d]);
+      load_round<FULLG>(a, rb.at(l.j), kb + l.j, mx, ny, l.u0, lane, buf[d]);
       pos[d] = it.take(rb);
     }
   }
   return cnt;
+}
+
+// T of column mx over the pixels of group g (the sums of the scan lengths the fused kernels do not
+// take, from full columns of G, chunk by chunk): the partial T of the group goes to part[g]
+// (column-major [mx][my], summed by the phase pass like the fused sum's).
+template <bool CHI0, bool FULLG, bool PWRITE>
+__global__ void __launch_bounds__(64 * kPrunedCols) k_psum(YArgs a, Optics o, int ny) {
+  if (state_unready(a)) return;
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  const int W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float2* t = (float2*)(s_dyn + (size_t)wave * pruned_wave_lds(ny));
+  const int nx = a.nx;
+  const int64_t wid = (int64_t)blockIdx.x * W + wave;
+  const PrunedItem pi = pruned_item(a, blockIdx.x, wave, W);
+  if (!pi.live) {
+    if (lane == 0 && !a.accumulate) a.wcnt[wid] = 0ull;
+    return;
+  }
+  const int mx = pi.mx, g = pi.g;
+  for (int i = lane; i < ny; i += 64) t[i] = make_float2(0.f, 0.f);
+  const WavePixels wp = wave_pixels(pi.kd_a, pi.kd_b, 0, 1);
+  unsigned long long cnt = 0;
+  for (int i0 = 0; i0 < wp.count; i0 += 64) {
+    const int kb = wp.kd_a + i0;
+    const int nb = min(64, wp.count - i0);
+    const RunBatch rb = make_batch(gather_run(a, o, kb, 1, nb, mx, lane, !CHI0, FULLG), nb);
+    cnt += sum_batch<CHI0, FULLG, PWRITE>(a, rb, kb, mx, ny, lane, t);
+  }
+  float2* pgp = a.part + (int64_t)g * nx * ny + (int64_t)mx * ny;
+  for (int i = lane; i < ny; i += 64) pgp[i] = a.accumulate ? cadd(pgp[i], t[i]) : t[i];
+  unsigned long long cc = cnt + (cnt << kLoadShift);  // one 8-byte load per pair
+  if (lane == 0) a.wcnt[wid] = a.accumulate ? a.wcnt[wid] + cc : cc;
 }
 
 // Refocus sum in balanced pieces.  The pruned array is column-major (the runs of a column's pixels
@@ -381,7 +421,7 @@ __global__ void __launch_bounds__(64 * kPrunedCols) k_psum_stream(YArgs a, Optic
       }
     }
     const RunBatch rb = make_batch(d, nb);
-    cnt += sum_batch<CHI0>(a, rb, 0, mx, ny, lane, t);
+    cnt += sum_batch<CHI0, false, false>(a, rb, 0, mx, ny, lane, t);
     i += nb;
     if (RunBatch::rl64(e1raw, nb - 1) >= E1 || i >= cend) break;
   }
@@ -645,7 +685,7 @@ __global__ void __launch_bounds__(64 * kAdjWaves) k_padj(YArgs a, Optics o, int 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float2* tb = (float2*)s_dyn;
   const int nx = a.nx;
-  const PrunedItem pi = pruned_item(a, blockIdx.x);
+  const PrunedItem pi = pruned_item(a, blockIdx.x, 0, 1);
   if (!pi.live) {
     if (wave == 0 && lane < 8 && !a.accumulate) a.pdc[(int64_t)blockIdx.x * 8 + lane] = 0.0;
     return;
@@ -743,8 +783,34 @@ inline int psum_waves(int ny) {
   return w;
 }
 
+// waves a launch writes partials for (wave index blockIdx.x * W + wave)
+inline int64_t psum_launch_waves(int ny, int nx, int ngroups) {
+  const int w = psum_waves(ny);
+  return (int64_t)((nx + w - 1) / w) * ngroups * w;
+}
+
 // dL/dc partials of an adjoint launch over the stored values (one per workgroup)
 inline int64_t padj_partials(int nx, int ngroups) { return (int64_t)nx * ngroups; }
+
+// a fit's sum at the other scan lengths over full columns of G at a.X (pixels from a.xk0), chunk by
+// chunk; pwrite: also store the values as the pruned array
+inline int launch_psum(int ny, const YArgs& a, const Optics& o, int chi0, bool pwrite, hipStream_t s) {
+  const int w = psum_waves(ny);
+  const size_t lds = (size_t)w * pruned_wave_lds(ny);
+  const dim3 grid((unsigned)(psum_launch_waves(ny, a.nx, a.ngroups) / w)), blk(64 * w);
+  STEM_TRACE("ssb_gsum", s);
+  auto go = [&](auto c0, auto pw) {
+    hipLaunchKernelGGL((k_psum<decltype(c0)::value, true, decltype(pw)::value>), grid, blk, lds, s, a, o, ny);
+  };
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  if (pwrite)
+    chi0 ? go(T_{}, T_{}) : go(F_{}, T_{});
+  else
+    chi0 ? go(T_{}, F_{}) : go(F_{}, F_{});
+  STEM_LAUNCH_CHECK();
+  return STEM_OK;
+}
 
 // Waves of the refocus sum in balanced pieces: the waves MI355X holds at once (256 compute units;
 // per unit the workgroups its 160 KB of LDS holds, at most 5 waves per SIMD by registers), so

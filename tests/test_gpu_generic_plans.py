@@ -5,12 +5,13 @@ to 512 threads (2048), a fast length beside another one, fewer pixels than a wor
 transform here)."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2104_06336_amd as stem
 from gen import C4_TRUE_ABERRATIONS, WORKLOADS, simulate
 from oracle import ssb as ossb
 
-from helpers import gpu_com, gpu_ssb, oracle_dpc, oracle_pruned, oracle_row_dft, oracle_ssb, rel_l2, state_pruned, state_X
+from helpers import gpu_com, gpu_ssb, oracle_dpc, oracle_pruned, oracle_row_dft, oracle_ssb, rel_l2, state_pruned, state_X, structs
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +48,35 @@ def test_plans(gpu, scan, bin_, bits, g_mode):
             assert np.array_equal(poff, poff_ref) and rel_l2(pg, pg_ref) <= TOL
     g = gpu_com(d_idx, d_off, wl, phase=True)
     assert rel_l2(g["phase"], oracle_dpc(idx, off, wl)) <= TOL
+
+
+@pytest.mark.parametrize("g_mode", [stem.STEM_G_STORE, stem.STEM_G_RECOMPUTE], ids=["store", "recompute"])
+@pytest.mark.parametrize("scan", [(48, 80), (54, 64)], ids=["48x80", "54x64"])
+def test_fit(gpu, scan, g_mode):
+    """SSBPhase on accumulated events: the phase, then dL/dc and dL/dtheta against the oracle gradient, at the
+    first coefficients (FINALIZE) and at others (from the stored values in STORE); 1e-4 per component, the
+    tolerance of every adjoint here."""
+    print(f"\n[gpu] fit {scan} mode {g_mode}", flush=True)
+    wl = WORKLOADS["small"].replace(name=f"fit {scan}", scan=scan, bin=2, mean_e=20.0)
+    d = simulate(wl, device="cuda")
+    d_idx, d_off = d.idx.contiguous(), d.off.contiguous()
+    idx, off = d_idx.cpu().numpy(), d_off.cpu().numpy()
+    det, sc, optics = structs(wl)
+    st = stem.SsbState(det, sc, optics, stem.Ssb(stem.STEM_FFT_FP32, 0, g_mode, 8, 1))
+    st.accumulate(d_idx, d_off, 0, wl.n_frames)
+    rng = np.random.default_rng(11)
+    th = rng.uniform(-0.3, 0.3, size=st.n_k).astype(np.float32)
+    for k in range(2):
+        c = tuple(np.array(C4_TRUE_ABERRATIONS) * (1 + rng.uniform(-0.5, 0.5, size=8)))
+        ct = torch.tensor(c, dtype=torch.float64, requires_grad=True)
+        tt = torch.from_numpy(th).cuda().requires_grad_(True)
+        phi = stem.SSBPhase.apply(ct, tt, st)
+        (-torch.var(phi, unbiased=False)).backward()
+        ref = oracle_ssb(idx, off, wl, c=c, theta=th)
+        assert int(st.status.item()) == 0
+        assert rel_l2(phi.detach().cpu().numpy(), ref["phi"]) <= TOL
+        dco, dtho = ossb.ssb_adjoint(ref["G"], ref["kc"], ossb.neg_var_grad(ref["phi"]), wl.step, wl.dk, wl.lam,
+                                     wl.r_bf, c, th)
+        dc = ct.grad.numpy()
+        assert np.all(np.abs(dc - dco) <= 1e-4 * np.abs(dco) + 1e-6 * np.max(np.abs(dco)))
+        assert rel_l2(tt.grad.cpu().numpy(), dtho) <= 1e-4
