@@ -473,25 +473,32 @@ int launch_geometry(const stem_det& det, double r2, RowRun* rows, double2* kc, h
 // ---------------------------------------------------------------------------------------------
 // binning into D[kd][f] (frames of whole scan rows)
 //
-// Workgroup = kBinFrames consecutive frames x a run of up to kBinKd kept pixels (small
-// workgroups: several per CU hide the latency of their load, count and write-out phases).  The block's
-// events are streamed in windows of kBinWin: first each thread writes its frame number into an
-// LDS byte map over the window's events, then the events are read with coalesced 16-byte loads
-// (four per lane), their frames read from the map as one word and their pixels mapped by the
-// lookup table.  Counts live in LDS: 8-bit counters, four frames per word, when every frame of
-// the block has at most 255 events (no count can then carry into its neighbour); otherwise
-// 16-bit counters, two frames per word, over two passes of half the pixels.  A count above the
-// element type of D sets STEM_EOVERFLOW (the stored value is then not meaningful).
+// Workgroup = FR consecutive frames x a run of up to BinShape<FR>::kKd kept pixels (small workgroups:
+// several per CU hide the latency of their load, count and write-out phases).  The block's events are
+// streamed in windows of kBinWin: first threads write the frame numbers into an LDS byte map over the
+// window's events, then the events are read with coalesced 16-byte loads (four per lane), their frames
+// read from the map as one word and their pixels mapped by the lookup table.  Counts live in LDS: 8-bit counters, four frames per word, when every frame of the block has at
+// most 255 events (no count can then carry into its neighbour); otherwise 16-bit counters, two frames
+// per word, over two passes of half the pixels.  A count above the element type of D sets
+// STEM_EOVERFLOW (the stored value is then not meaningful).
+//
+// FR = 128 writes whole 128-byte lines of D.  Where its counters do not hold all kept pixels, every chunk
+// of pixels would read and look up the block's events again: FR = 64 and 32 hold 351 and 800 pixels at
+// once (launch_bin's rule).
 
-constexpr int kBinFrames = 128;
 constexpr int kBinThreads = 256;
-constexpr int kBinWords = 5976;                       // 23 KB of counters
-// pixel rows of counters are kBinFrames/4 (+1 padding) words apart, so that the events of one
-// frame (same column, different pixels) fall into different LDS banks
-constexpr int kBinKd = kBinWords / (kBinFrames / 4 + 1);  // 181 pixels per workgroup
-constexpr int kBinWin = 6144;                         // events per window of the frame map (a block of
-                                                      // 128 frames at 40 events per frame fits one)
-constexpr int kBinBoxMax = 4096;                      // bins of the largest LDS bin table (8 KB)
+constexpr int kBinWin = 6144;       // events per window of the frame map (a block of 128 frames at 40
+                                    // events per frame fits one)
+constexpr int kBinBoxMax = 4096;    // bins of the largest LDS bin table (8 KB)
+
+// Counters of a workgroup of FR frames: words of LDS (23 or 28 KB), and the pixels they hold.  Pixel rows
+// of counters are FR/4 (+1 padding) words apart, so that the events of one frame (same column,
+// different pixels) fall into different LDS banks.
+template <int FR>
+struct BinShape {
+  static constexpr int kWords = FR == 32 ? 7200 : 5976;
+  static constexpr int kKd = kWords / (FR / 4 + 1);  // 181, 351, 800
+};
 
 // The kept bins' bounding box (in bins) and the divisions that take a pixel to its bin: with it
 // (BOX) the pixel -> bin table is a small per-workgroup LDS copy over the box, looked up with a
@@ -506,13 +513,11 @@ struct BinBox {
   int32_t start[kBoxRows], lo[kBoxRows], hi[kBoxRows];  // row runs of the box's rows (BOX)
 };
 
-// The kept set's geometry, written by the first workgroup of the binning kernel (BOX: the
-// binning itself takes the box's row runs from its arguments)
+// The kept set's geometry, written by the first workgroup of the binning kernel (BOX)
 struct GeomOut {
   RowRun* rows;       // nullptr: nothing to write
   double2* kc;
-  int32_t nbx, nby, cx, cy;
-  double r2;
+  int32_t nby, cx, cy;
   unsigned long long* mark;  // if set, cleared by the first thread (an accumulation from frame 0
                              // voids the state's FINALIZE)
 };
@@ -538,68 +543,102 @@ __device__ __forceinline__ void seg_step(int key, int32_t& ax, int32_t& ay) {
 // holds at most kBinWin events, each |kx - cx| < 2^16), which thread f folds into its frame's
 // int64 sums at the next window barrier.  The centre of mass is then S / N_f by one double
 // division, as the centre-of-mass kernel computes it.
-template <typename DT, bool BOX, bool COM>
+//
+// BOX: the first nset workgroups bin nothing; the first writes the geometry, the others the interval table
+// and the mask (with B >= 4 columns a set, one word per workgroup and every fourth column per wave, else
+// one word per wave), beside the binning's rather than before it.
+template <typename DT, bool BOX, bool COM, int FR>
 __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__ idx,
                                                      const int64_t* __restrict__ off, int64_t frame0,
                                                      int64_t n_frames, int32_t npix,
                                                      const int16_t* __restrict__ lut,
                                                      const RowRun* __restrict__ rows, BinBox box, int32_t n_k,
                                                      int64_t F, DT* __restrict__ D, ComOut com, GeomOut geo,
-                                                     SetsJob sj, int32_t* status) {
+                                                     SetsJob sj, int nset, int64_t fblocks, int32_t* status) {
+  constexpr int kKd = BinShape<FR>::kKd;
   extern __shared__ int16_t s_box[];  // [bh][bw] kept-bin index of each bin of the box, or -1
-  __shared__ __align__(16) uint32_t s_hist[kBinWords];
+  __shared__ __align__(16) uint32_t s_hist[BinShape<FR>::kWords];
   __shared__ uint32_t s_map[(kBinWin + 16) / 4];
-  __shared__ int32_t s_rel[kBinFrames + 1];
-  __shared__ int64_t s_base;
-  __shared__ int32_t s_mom[COM ? 2 * kBinFrames : 1];  // [x | y][frame] moment sums of a window
+  __shared__ int64_t s_off[FR + 1];
+  __shared__ int32_t s_mom[COM ? 2 * FR : 1];  // [x | y][frame] moment sums of a window
   const int t = threadIdx.x;
   const int lane = t & 63;
   if (geo.mark && blockIdx.x == 0 && t == 0) *geo.mark = 0ull;
-  if (geo.rows && blockIdx.x == 0) {
-    // the counters' LDS is free until the first pass clears it
-    build_geometry(box.bin, geo.nbx, geo.nby, geo.cx, geo.cy, geo.r2, geo.rows, geo.kc, (int32_t*)s_hist);
-    __syncthreads();
-  }
   if constexpr (BOX) {
-    // workgroups 1, 2, ... build the interval table and the mask, one word per wave, with Kc of
-    // the lane's pixel from the box's row runs (as the geometry computes it)
-    const int64_t word = (int64_t)(blockIdx.x - 1) * (kBinThreads / 64) + (t >> 6);
-    if (sj.cst && blockIdx.x >= 1 && word < (int64_t)sj.ncs * sj.nmw) {
-      const int kd = 64 * (int)(word % sj.nmw) + lane;
-      double2 k = make_double2(0.0, 0.0);
-      if (kd < sj.n_k) {
+    if ((int)blockIdx.x < nset) {
+      // Kc of kept pixel kd from the box's row runs
+      auto centre = [&](int kd) {
         int r = 0;
         while (r < box.bh - 1 && kd >= box.start[r] + box.hi[r] - box.lo[r]) ++r;
-        k = make_double2(bin_centre(box.bin, box.lo[r] + kd - box.start[r], geo.cx),
-                         bin_centre(box.bin, box.by0 + r, geo.cy));
+        return make_double2(bin_centre(box.bin, box.lo[r] + kd - box.start[r], geo.cx),
+                            bin_centre(box.bin, box.by0 + r, geo.cy));
+      };
+      if (blockIdx.x == 0) {
+        for (int r = t; r < geo.nby; r += kBinThreads) {
+          const int q = r - box.by0;
+          const bool in = q >= 0 && q < box.bh;
+          geo.rows[r] = in ? RowRun{box.start[q], box.lo[q], box.hi[q], 0} : RowRun{q < 0 ? 0 : n_k, 0, 0, 0};
+        }
+        for (int kd = t; kd < n_k; kd += kBinThreads) geo.kc[kd] = centre(kd);
+        return;
       }
-      sets_word(sj, word, lane, k);
+      const int w = t >> 6;
+      const bool split = sj.B >= 4;
+      const int64_t word = split ? (int64_t)blockIdx.x - 1 : (int64_t)(blockIdx.x - 1) * (kBinThreads / 64) + w;
+      const bool live = word < (int64_t)sj.ncs * sj.nmw;  // the same for the whole wave
+      uint64_t bits = 0;
+      if (live) {
+        const int kd = 64 * (int)(word % sj.nmw) + lane;
+        const double2 k = kd < sj.n_k ? centre(kd) : make_double2(0.0, 0.0);
+        bits = sets_columns(sj, word, lane, k, split ? w : 0, split ? 4 : 1);
+      }
+      if (split) {
+        uint64_t* s_bits = (uint64_t*)s_hist;
+        if (lane == 0) s_bits[w] = bits;
+        __syncthreads();
+        bits = s_bits[0] | s_bits[1] | s_bits[2] | s_bits[3];
+        if (t == 0 && live) sj.mask[word] = bits;
+      } else if (lane == 0 && live) {
+        sj.mask[word] = bits;
+      }
+      return;
     }
   }
-  // workgroups added for the table only (tiny scans) bin nothing
-  if ((int64_t)(blockIdx.x / ((n_k + kBinKd - 1) / kBinKd)) * kBinFrames >= n_frames) return;
-  const int nchunks = (n_k + kBinKd - 1) / kBinKd;
-  const int kd0 = (int)(blockIdx.x % nchunks) * kBinKd;
-  const int kc = n_k - kd0 < kBinKd ? n_k - kd0 : kBinKd;
-  const int64_t fb = frame0 + (int64_t)(blockIdx.x / nchunks) * kBinFrames;
+  const int nchunks = (n_k + kKd - 1) / kKd;
+  const int64_t blk = (int64_t)blockIdx.x - nset;
+  const int kd0 = (int)(blk % nchunks) * kKd;
+  const int kc = n_k - kd0 < kKd ? n_k - kd0 : kKd;
+  int64_t fblk = blk / nchunks;
+  // Blocks of less than 128 frames share D's 128-byte lines with their neighbours: consecutive ones go to
+  // the same XCD (workgroups go round the 8 of them), whose L2 then joins the parts of a line.
+  if (FR < 128 && nchunks == 1 && (fblocks & 7) == 0) fblk = (fblk & 7) * (fblocks >> 3) + (fblk >> 3);
+  const int64_t fb = frame0 + fblk * FR;
   const int64_t fend = frame0 + n_frames;
-  const int nf = (int)((fend - fb) < kBinFrames ? (fend - fb) : kBinFrames);
-  if (!load_rel_offsets(off, fb, nf, s_rel, &s_base, status)) return;
+  const int nf = (int)((fend - fb) < FR ? (fend - fb) : FR);
+  if (t <= nf) s_off[t] = off[fb + t];
   const bool com_blk = COM && kd0 == 0;  // workgroup-uniform
   if constexpr (COM) {
     if (com_blk)
-      for (int i = t; i < 2 * kBinFrames; i += kBinThreads) s_mom[i] = 0;
+      for (int i = t; i < 2 * FR; i += kBinThreads) s_mom[i] = 0;
   }
   int64_t msx = 0, msy = 0;  // thread t: the moments of frame t so far
   // after a barrier that follows a window's atomics and precedes the next window's
   auto fold_moments = [&]() {
-    if (COM && com_blk && t < kBinFrames) {
+    if (COM && com_blk && t < FR) {
       msx += s_mom[t];
-      msy += s_mom[kBinFrames + t];
+      msy += s_mom[FR + t];
       s_mom[t] = 0;
-      s_mom[kBinFrames + t] = 0;
+      s_mom[FR + t] = 0;
     }
   };
+  __syncthreads();
+  const int64_t base = s_off[0];
+  if (s_off[nf] - base >= (1ll << 30)) {  // the 32-bit relative offsets cannot address that many events
+    if (t == 0) report(status, STEM_EOVERFLOW);
+    return;
+  }
+  const int span = (int)(s_off[nf] - base);
+  constexpr int U = kBinWin / (4 * kBinThreads);  // 16-byte groups per thread in flight: one pass per window
   if constexpr (BOX) {
     // kept index of each bin of the box from the row runs (the rule of the per-pixel table)
     for (int i = t; i < box.bw * box.bh; i += kBinThreads) {
@@ -607,20 +646,22 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
       s_box[i] = (int16_t)(bx >= box.lo[ry] && bx < box.hi[ry] ? box.start[ry] + bx - box.lo[ry] : -1);
     }
   }
-  __syncthreads();
-  const int wide = __syncthreads_or(t < nf && s_rel[t + 1] - s_rel[t] > 255);
-  const int span = s_rel[nf];
-  const int lo_t = t < nf ? s_rel[t] : 0, hi_t = t < nf ? s_rel[t + 1] : 0;
-  const int64_t base = s_base;
+  const int wide = __syncthreads_or(t < nf && s_off[t + 1] - s_off[t] > 255);
+  // the frame whose map entries this thread writes, with the kBinThreads / FR - 1 threads beside it
+  constexpr int S = kBinThreads / FR;
+  const int mf = t / S, mp = t % S;
+  const int lo_m = mf < nf ? (int)(s_off[mf] - base) : 0, hi_m = mf < nf ? (int)(s_off[mf + 1] - base) : 0;
   uint8_t* map = (uint8_t*)s_map;
   int32_t bad = 0;
   const int npass = wide ? 2 : 1;
   const int kpp = (kc + npass - 1) / npass;       // pixels per pass
-  const int wpr = wide ? kBinFrames / 2 : kBinFrames / 4;  // words per pixel row
+  const int wpr = wide ? FR / 2 : FR / 4;         // words per pixel row
   const int wps = wpr + 1;                        // row stride in words (padded)
   const uint32_t cap = sizeof(DT) == 1 ? 255u : 65535u;
-  // 8-bit counts go out as 16 frames (four counter words) per 16-byte store when aligned
-  const bool vec = sizeof(DT) == 1 && !wide && (((uintptr_t)D & 15) == 0) && (F & 15) == 0 && (fb & 15) == 0;
+  // 8-bit counts go out as 16 frames (four counter words) per 16-byte store, 16-bit ones as 4 frames (one
+  // word) per 8-byte store, when aligned
+  const bool vec = !wide && (((uintptr_t)D & 15) == 0) &&
+                   (sizeof(DT) == 1 ? (F & 15) == 0 && (fb & 15) == 0 : (F & 3) == 0 && (fb & 3) == 0);
   for (int pass = 0; pass < npass; ++pass) {
     const int ka = kd0 + pass * kpp;
     const int kn = (kd0 + kc) - ka < kpp ? (kd0 + kc) - ka : kpp;
@@ -629,31 +670,38 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
       const int wn = span - w0 < kBinWin ? span - w0 : kBinWin;
       const int64_t a0 = base + w0;
       const int sh = (int)((((uintptr_t)(idx + a0)) & 15) >> 2);  // map[sh + j] <-> event a0 + j
-      __syncthreads();
-      fold_moments();
+      if (w0 > 0) {
+        __syncthreads();
+        fold_moments();
+      }
       {
-        // frame t's events of this window: map entries [lo, hi)
-        const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
-        const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
-        int j = lo;
-        for (; j < hi && (j & 3); ++j) map[j] = (uint8_t)t;
-        const uint32_t word = (uint32_t)(t & 0xff) * 0x01010101u;
-        for (; j + 4 <= hi; j += 4) s_map[j >> 2] = word;
-        for (; j < hi; ++j) map[j] = (uint8_t)t;
+        // frame mf's events of this window: map entries [lo, hi), words shared out among its threads
+        const int lo = (lo_m > w0 ? lo_m : w0) - w0 + sh;
+        const int hi = (hi_m < w0 + wn ? hi_m : w0 + wn) - w0 + sh;
+        const uint32_t word = (uint32_t)mf * 0x01010101u;
+        if (lo < hi)
+          for (int i = (lo >> 2) + mp; 4 * i < hi; i += S) {
+            if (4 * i >= lo && 4 * i + 4 <= hi) {
+              s_map[i] = word;
+            } else {
+              for (int j = max(4 * i, lo); j < min(4 * i + 4, hi); ++j) map[j] = (uint8_t)mf;
+            }
+          }
       }
       __syncthreads();
       // Positions p = 4 g + q of the 16-byte aligned run from ib: [sh, sh + wn) are this window's
       // events.  Every group g < ng holds at least one of them, so its whole 16-byte line lies in
-      // the event array's pages; the other positions of the line are masked out.
+      // the event array's pages; the other positions of the line are masked out.  (Loaded before the
+      // map is written, the events cost 12 registers and a wave per SIMD: 121 against 104 us at
+      // 1024 x 1024, 59 against 52 us at 512 x 512 binned 6x.)
       const int32_t* ib = idx + (a0 - sh);
       const int ng = (wn + sh + 3) >> 2;
-      constexpr int U = kBinWin / (4 * kBinThreads);  // groups per thread in flight: one pass per window
-      for (int g0 = t; g0 < ng; g0 += U * kBinThreads) {
+      {
         int4 kv[U];
         uint32_t fr4[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int g = g0 + u * kBinThreads;
+          const int g = t + u * kBinThreads;
           kv[u] = make_int4(0, 0, 0, 0);
           fr4[u] = 0u;
           if (g < ng) {
@@ -667,7 +715,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const int p = 4 * (g0 + u * kBinThreads) + q;
+            const int p = 4 * (t + u * kBinThreads) + q;
             const int k = q == 0 ? kv[u].x : q == 1 ? kv[u].y : q == 2 ? kv[u].z : kv[u].w;
             const bool ok = (uint32_t)(p - sh) < (uint32_t)wn;
             const bool in = (uint32_t)k < (uint32_t)npix;
@@ -694,14 +742,14 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
               int32_t ax = 0, ay = 0;
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
-                const int p = 4 * (g0 + u * kBinThreads) + q;
+                const int p = 4 * (t + u * kBinThreads) + q;
                 if ((uint32_t)(p - sh) >= (uint32_t)wn) continue;
                 const int k = q == 0 ? kv[u].x : q == 1 ? kv[u].y : q == 2 ? kv[u].z : kv[u].w;
                 const int f = (int)((fr4[u] >> (8 * q)) & 0xffu);
                 if (f != fc) {
                   if (fc >= 0) {
                     atomicAdd(&s_mom[fc], ax);
-                    atomicAdd(&s_mom[kBinFrames + fc], ay);
+                    atomicAdd(&s_mom[FR + fc], ay);
                   }
                   fc = f;
                   ax = ay = 0;
@@ -715,19 +763,19 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
               }
               // the lanes' last runs: inclusive scan within each row of 16 lanes, segmented by
               // frame, by DPP row shifts (register moves, no LDS traffic); lower lanes hold
-              // earlier events, and the lanes of this loop trip are a prefix of the wave
+              // earlier events
               const int key = fc >= 0 ? fc : 256 + lane;  // a lane without events merges with none
               seg_step<0x111>(key, ax, ay);               // row_shr:1
               seg_step<0x112>(key, ax, ay);               // row_shr:2
               seg_step<0x114>(key, ax, ay);               // row_shr:4
               seg_step<0x118>(key, ax, ay);               // row_shr:8
               // a run ends where the next lane's frame differs, at a row's last lane (row_shl:1
-              // leaves the sentinel there) and before a lane outside this loop trip
+              // leaves the sentinel there) and after the window's last group
               const int nkey = __builtin_amdgcn_update_dpp(-2, key, 0x101, 0xf, 0xf, false);
-              const bool last = g0 + 1 >= ng || nkey != key;
+              const bool last = t + u * kBinThreads + 1 >= ng || nkey != key;
               if (fc >= 0 && last) {
                 atomicAdd(&s_mom[fc], ax);
-                atomicAdd(&s_mom[kBinFrames + fc], ay);
+                atomicAdd(&s_mom[FR + fc], ay);
               }
             }
           }
@@ -746,7 +794,20 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
       }
     }
     __syncthreads();
-    if (vec) {
+    if (vec && sizeof(DT) == 2) {
+      // one counter word (4 frames) of one pixel row per thread and step
+      for (int i = t; i < kn * wpr; i += kBinThreads) {
+        const int kd = i / wpr, q = i % wpr;
+        const int f0 = 4 * q;
+        if (f0 >= nf) continue;
+        const uint32_t w = s_hist[kd * wps + q];
+        DT* dst = D + (int64_t)(ka + kd) * F + (fb + f0);
+        if (f0 + 4 <= nf)
+          *(uint2*)dst = make_uint2((w & 0xffu) | ((w & 0xff00u) << 8), ((w >> 16) & 0xffu) | ((w >> 24) << 16));
+        else
+          for (int j = 0; f0 + j < nf; ++j) dst[j] = (DT)((w >> (8 * j)) & 0xffu);
+      }
+    } else if (vec) {
       // four counter words (16 frames) of one pixel row per thread and step
       const int qpr = wpr / 4;
       for (int i = t; i < kn * qpr; i += kBinThreads) {
@@ -793,7 +854,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
     fold_moments();  // the pass loop ends with a barrier: the last window's sums
     if (com_blk && t < nf) {
       const int64_t fr = fb + t;
-      const int64_t n = hi_t - lo_t;
+      const int64_t n = s_off[t + 1] - s_off[t];
       const int64_t sx = msx, sy = msy;
       const double x = n > 0 ? (double)sx / (double)n : 0.0;
       const double y = n > 0 ? (double)sy / (double)n : 0.0;
@@ -857,26 +918,35 @@ int launch_bin(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
                void* D, int d_bits, int32_t* status, hipStream_t stream, const ComOut* com, const SetsJob* sets,
                unsigned long long* mark) {
   if (n_frames == 0) return STEM_OK;
-  const int nchunks = (n_k + kBinKd - 1) / kBinKd;
-  const int64_t fblocks = (n_frames + kBinFrames - 1) / kBinFrames;
-  const int nbx = det.W / det.bin, nby = det.H / det.bin;
   BinBox box;
   const bool use_box = make_box(det, r2, box);
   const int64_t cells = (int64_t)box.bw * box.bh;
   const size_t lds = use_box ? (size_t)((cells * 2 + 15) & ~15ll) : 0;
-  // BOX with the interval table: enough workgroups for one wave per mask word besides the first
+  // BOX: a workgroup for the geometry and those of the interval table, a multiple of 8 (the rest follow in
+  // the order of the XCDs)
   const SetsJob sj = use_box && sets ? *sets : SetsJob{};
-  int64_t blocks = fblocks * nchunks;
-  if (sj.cst) {
-    const int64_t need = 1 + ((int64_t)sj.ncs * sj.nmw + kBinThreads / 64 - 1) / (kBinThreads / 64);
-    if (need > blocks) blocks = need;
+  int nset = 0;
+  if (use_box) {
+    const int64_t words = sj.cst ? (int64_t)sj.ncs * sj.nmw : 0;
+    nset = (int)((1 + (sj.B >= 4 ? words : (words + kBinThreads / 64 - 1) / (kBinThreads / 64)) + 7) & ~7ll);
   }
-  const dim3 grid((unsigned)blocks);
+  // Frames per workgroup: 128; less where that takes fewer chunks of pixels.  Measured (one MI355X, 576 x 576
+  // detector, FR = 128 / 64 / 32): 256 x 256 scan, 707 pixels, 77 / 71 / 37 us; 512 x 512, 314 pixels, 95 / 56
+  // / 93 us; 1024 x 1024, 176 pixels (one chunk with any), 106 / 167 / 319 us.
+  auto chunks_of = [&](int fr) {
+    const int kd = fr == 128 ? BinShape<128>::kKd : fr == 64 ? BinShape<64>::kKd : BinShape<32>::kKd;
+    return (n_k + kd - 1) / kd;
+  };
+  auto blocks_of = [&](int fr) { return (n_frames + fr - 1) / fr; };
+  int fr = 128;
+  while (fr > 32 && chunks_of(fr / 2) < chunks_of(fr)) fr /= 2;
+  const int64_t fblocks = blocks_of(fr);
+  const dim3 grid((unsigned)(nset + fblocks * chunks_of(fr)));
   // BOX: the binning kernel's first workgroup writes the row runs and bin centres; otherwise the
   // per-pixel table needs them first
   GeomOut geo{};
   if (use_box) {
-    geo = GeomOut{rows, kc, nbx, nby, det.cx, det.cy, r2, nullptr};
+    geo = GeomOut{rows, kc, det.H / det.bin, det.cx, det.cy, nullptr};
   } else {
     if (int st = launch_geometry(det, r2, rows, kc, stream)) return st;
     // the per-pixel table, read by the binning kernel
@@ -890,11 +960,17 @@ int launch_bin(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
   STEM_TRACE(com ? "bin_com" : "bin_densify", stream);
   const ComOut co = com ? *com : ComOut{};
   const int npix = det.W * det.H;
-  auto go = [&](auto dt, auto bx, auto cm) {
+  auto launch = [&](auto dt, auto bx, auto cm, auto frames) {
     using DT = decltype(dt);
     constexpr bool BX = decltype(bx)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_bin<DT, BX, CM>), grid, dim3(kBinThreads), BX ? lds : 0, stream, idx, off, frame0,
-                       n_frames, npix, lut, rows, box, n_k, F, (DT*)D, co, geo, sj, status);
+    hipLaunchKernelGGL((k_bin<DT, BX, CM, decltype(frames)::value>), grid, dim3(kBinThreads), BX ? lds : 0, stream, idx,
+                       off, frame0, n_frames, npix, lut, rows, box, n_k, F, (DT*)D, co, geo, sj, nset, fblocks,
+                       status);
+  };
+  auto go = [&](auto dt, auto bx, auto cm) {
+    if (fr == 128) launch(dt, bx, cm, std::integral_constant<int, 128>{});
+    else if (fr == 64) launch(dt, bx, cm, std::integral_constant<int, 64>{});
+    else launch(dt, bx, cm, std::integral_constant<int, 32>{});
   };
   using T_ = std::true_type;
   using F_ = std::false_type;

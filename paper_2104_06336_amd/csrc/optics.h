@@ -9,6 +9,7 @@ struct Optics {
   double lam, dk, r, r2;
   double c[8];
   double sx, sy;  // detector pixels per scan-frequency index along x and y
+  double rsy;     // 1 / sy
   // chi as a polynomial in (wx, wy) = lam*dk*(kx, ky):  p20 wx^2 + p02 wy^2 + p11 wx wy
   //   + p30 wx^3 + p21 wx^2 wy + p12 wx wy^2 + p03 wy^3 + p4 (wx^2 + wy^2)^2
   double lk;
@@ -131,7 +132,8 @@ __device__ __forceinline__ bool near_disk(double kx, double ky, double qx, doubl
 
 // Interval of iy in [lo, hi] (inclusive) where near_disk holds along the column Qx = qx; empty
 // when lo_out > hi_out.  ny: number of frequencies (iy in [-ny/2, ny/2)).
-__device__ __forceinline__ void disk_interval(double kx, double ky, double qx, double sy, double r, double r2, int sgn,
+// (rsy = 1/sy: it only enters the estimates, which the exact test corrects.)
+__device__ __forceinline__ void disk_interval(double kx, double ky, double qx, double sy, double rsy, double r2, int sgn,
                                               int ny, int& lo_out, int& hi_out) {
   const int imin = -ny / 2, imax = ny / 2 - 1;
   // centre: Qy = -sgn*... (K - Q: Qy = Ky; K + Q: Qy = -Ky)
@@ -142,10 +144,10 @@ __device__ __forceinline__ void disk_interval(double kx, double ky, double qx, d
   hi_out = 0;
   if (!(h2 > -1e-9 * r2)) return;  // |dx| well beyond r: empty (the exact test is checked at the centre)
   const double h = sqrt(h2 > 0.0 ? h2 : 0.0);
-  int c0 = (int)floor(cy / sy);
+  int c0 = (int)floor(cy * rsy);
   if (c0 < imin) c0 = imin;
   if (c0 > imax) c0 = imax;
-  // the minimum of the V lies at c0 or a neighbour (c0 = floor(cy/sy) may be off by one after
+  // the minimum of the V lies at c0 or a neighbour (c0 = floor(cy rsy) may be off by one after
   // rounding); if the test fails at all three the set is empty
   int c = c0;
   if (!near_disk(kx, ky, qx, (double)c * sy, r2, sgn)) {
@@ -156,12 +158,12 @@ __device__ __forceinline__ void disk_interval(double kx, double ky, double qx, d
     }
   }
   // upper end: estimate, then walk to the exact boundary
-  int u = (int)floor((cy + h) / sy);
+  int u = (int)floor((cy + h) * rsy);
   if (u < c) u = c;
   if (u > imax) u = imax;
   while (u > c && !near_disk(kx, ky, qx, (double)u * sy, r2, sgn)) --u;
   while (u < imax && near_disk(kx, ky, qx, (double)(u + 1) * sy, r2, sgn)) ++u;
-  int l = (int)ceil((cy - h) / sy);
+  int l = (int)ceil((cy - h) * rsy);
   if (l > c) l = c;
   if (l < imin) l = imin;
   while (l < c && !near_disk(kx, ky, qx, (double)l * sy, r2, sgn)) ++l;
@@ -240,13 +242,13 @@ struct ColSet {
 __device__ __forceinline__ ColSet col_set(double kx, double ky, int ix, int ny, const Optics& o) {
   const double qx = (double)ix * o.sx;
   ColSet cs;
-  disk_interval(kx, ky, qx, o.sy, o.r, o.r2, -1, ny, cs.a0, cs.a1);
+  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, -1, ny, cs.a0, cs.a1);
   if (cs.a0 > cs.a1) {
     cs.b0 = 1;
     cs.b1 = 0;
     return cs;
   }
-  disk_interval(kx, ky, qx, o.sy, o.r, o.r2, +1, ny, cs.b0, cs.b1);
+  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, +1, ny, cs.b0, cs.b1);
   return cs;
 }
 
@@ -266,8 +268,10 @@ struct SetsJob {
 // (one column for the lengths those kernels do not take).
 __host__ __device__ inline int colset_width(int ny) { return (ny >= 32 && ny <= 1024 && (ny & (ny - 1)) == 0) ? 1024 / ny : 1; }
 
-// One mask word (one wave, every lane active); k = Kc of the lane's pixel when kd < n_k.
-__device__ __forceinline__ void sets_word(const SetsJob& j, int64_t word, int lane, double2 k) {
+// Columns from, from + step, ... of one mask word's set (one wave, every lane active); k = Kc of the lane's
+// pixel when kd < n_k.  Returns the mask bits of those columns.
+__device__ __forceinline__ uint64_t sets_columns(const SetsJob& j, int64_t word, int lane, double2 k, int from,
+                                                 int step) {
   const int nc = j.nx / 2 + 1, B = j.B;
   const int cs = (int)(word / j.nmw), w = (int)(word % j.nmw);
   const int kd = 64 * w + lane;
@@ -275,7 +279,7 @@ __device__ __forceinline__ void sets_word(const SetsJob& j, int64_t word, int la
   bool any = false;
   if (kd < j.n_k) {
     const int c1 = cs * B + B < nc ? cs * B + B : nc;
-    for (int c = cs * B; c < c1; ++c) {
+    for (int c = cs * B + from; c < c1; c += step) {
       const ColSet d = col_set(k.x, k.y, signed_index(c, j.nx), j.ny, j.o);
       ColSet m{1, 0, 1, 0};
       if (c > 0 && 2 * c < j.nx) m = col_set(k.x, k.y, signed_index(j.nx - c, j.nx), j.ny, j.o);
@@ -283,7 +287,12 @@ __device__ __forceinline__ void sets_word(const SetsJob& j, int64_t word, int la
       any = any || d.a0 <= d.a1 || m.a0 <= m.a1;
     }
   }
-  const uint64_t bits = __ballot(any);
+  return __ballot(any);
+}
+
+// One mask word and its columns.
+__device__ __forceinline__ void sets_word(const SetsJob& j, int64_t word, int lane, double2 k) {
+  const uint64_t bits = sets_columns(j, word, lane, k, 0, 1);
   if (lane == 0) j.mask[word] = bits;
 }
 

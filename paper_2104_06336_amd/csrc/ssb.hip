@@ -525,6 +525,7 @@ static Optics make_optics(const stem_optics& op, const stem_scan& sc) {
   for (int j = 0; j < 8; ++j) o.c[j] = op.c[j];
   o.sx = 1.0 / (((double)sc.nx * sc.step) * op.dk);
   o.sy = 1.0 / (((double)sc.ny * sc.step) * op.dk);
+  o.rsy = 1.0 / o.sy;
   optics_poly(o);
   optics_screen(o, sc.ny, sc.nx);
   return o;
