@@ -638,7 +638,6 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
     return;
   }
   const int span = (int)(s_off[nf] - base);
-  constexpr int U = kBinWin / (4 * kBinThreads);  // 16-byte groups per thread in flight: one pass per window
   if constexpr (BOX) {
     // kept index of each bin of the box from the row runs (the rule of the per-pixel table)
     for (int i = t; i < box.bw * box.bh; i += kBinThreads) {
@@ -696,12 +695,14 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
       // 1024 x 1024, 59 against 52 us at 512 x 512 binned 6x.)
       const int32_t* ib = idx + (a0 - sh);
       const int ng = (wn + sh + 3) >> 2;
-      {
+      constexpr int U = kBinWin / (4 * kBinThreads);  // groups per thread in flight: one trip per window (a
+                                                      // full one off a 16-byte line has a group more)
+      for (int g0 = t; g0 < ng; g0 += U * kBinThreads) {
         int4 kv[U];
         uint32_t fr4[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int g = t + u * kBinThreads;
+          const int g = g0 + u * kBinThreads;
           kv[u] = make_int4(0, 0, 0, 0);
           fr4[u] = 0u;
           if (g < ng) {
@@ -715,7 +716,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const int p = 4 * (t + u * kBinThreads) + q;
+            const int p = 4 * (g0 + u * kBinThreads) + q;
             const int k = q == 0 ? kv[u].x : q == 1 ? kv[u].y : q == 2 ? kv[u].z : kv[u].w;
             const bool ok = (uint32_t)(p - sh) < (uint32_t)wn;
             const bool in = (uint32_t)k < (uint32_t)npix;
@@ -742,7 +743,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
               int32_t ax = 0, ay = 0;
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
-                const int p = 4 * (t + u * kBinThreads) + q;
+                const int p = 4 * (g0 + u * kBinThreads) + q;
                 if ((uint32_t)(p - sh) >= (uint32_t)wn) continue;
                 const int k = q == 0 ? kv[u].x : q == 1 ? kv[u].y : q == 2 ? kv[u].z : kv[u].w;
                 const int f = (int)((fr4[u] >> (8 * q)) & 0xffu);
@@ -763,16 +764,16 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
               }
               // the lanes' last runs: inclusive scan within each row of 16 lanes, segmented by
               // frame, by DPP row shifts (register moves, no LDS traffic); lower lanes hold
-              // earlier events
+              // earlier events, and the lanes of this loop trip are a prefix of the wave
               const int key = fc >= 0 ? fc : 256 + lane;  // a lane without events merges with none
               seg_step<0x111>(key, ax, ay);               // row_shr:1
               seg_step<0x112>(key, ax, ay);               // row_shr:2
               seg_step<0x114>(key, ax, ay);               // row_shr:4
               seg_step<0x118>(key, ax, ay);               // row_shr:8
               // a run ends where the next lane's frame differs, at a row's last lane (row_shl:1
-              // leaves the sentinel there) and after the window's last group
+              // leaves the sentinel there) and before a lane outside this loop trip
               const int nkey = __builtin_amdgcn_update_dpp(-2, key, 0x101, 0xf, 0xf, false);
-              const bool last = t + u * kBinThreads + 1 >= ng || nkey != key;
+              const bool last = g0 + 1 >= ng || nkey != key;
               if (fc >= 0 && last) {
                 atomicAdd(&s_mom[fc], ax);
                 atomicAdd(&s_mom[FR + fc], ay);

@@ -1,7 +1,8 @@
 """Binning workgroups of 128, 64 and 32 frames (by the number of kept pixels) at the edges of each: the last
 number of pixels one workgroup holds and the first it does not, frame blocks that are not whole, whole
-scans and row chunks, 8- and 16-bit counts, and frames of more than 255 events (16-bit counters in two
-passes).  The cube is compared with the oracle's bit for bit."""
+scans and row chunks, 8- and 16-bit counts, blocks of one and of several windows of events, and frames of
+more than 255 events (16-bit counters in two passes).  The centre of mass of the same pass is compared
+with the oracle's too.  The cube is compared with the oracle's bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -32,8 +33,8 @@ def test_cube(gpu, n_k, bin_, scan, bits):
     kc, lut = oeer.bin_geometry(W, W, bin_, r)
     F = scan[0] * scan[1]
     rng = np.random.default_rng(n_k)
-    for pile in (0, 300):
-        n = rng.integers(0, 40, size=F)
+    for pile, most in ((0, 40), (300, 40), (0, 255)):
+        n = rng.integers(0, most, size=F)  # up to 254: several windows per block, most not on a 16-byte line
         if pile:
             n[[0, F // 2, F - 1]] = pile  # past 255 events: the 16-bit counters
         off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
@@ -47,8 +48,12 @@ def test_cube(gpu, n_k, bin_, scan, bits):
         d_idx, d_off = torch.from_numpy(idx).cuda(), torch.from_numpy(off).cuda()
         for rows in (scan[0], 5):
             st.region(stem.STEM_REGION_D).fill_(77)
+            com = torch.zeros(2 * F, dtype=torch.float64, device="cuda") if rows == 5 else None
             for y in range(0, scan[0], rows):
-                st.accumulate(d_idx, d_off, y * scan[1], min(rows, scan[0] - y) * scan[1])
+                st.accumulate(d_idx, d_off, y * scan[1], min(rows, scan[0] - y) * scan[1], com64=com)
             D = st.region(stem.STEM_REGION_D).view(torch.uint8 if bits == 8 else torch.int16).cpu().numpy()
             assert int(st.status.item()) == 0
             assert np.array_equal(D.reshape(len(kc), F).astype(np.int64), np.asarray(ref).astype(np.int64))
+            if com is not None:
+                cx, cy, *_ = oeer.com(idx, off, W, W)
+                assert np.array_equal(com.cpu().numpy().reshape(2, F), np.stack([cx, cy]))
