@@ -748,6 +748,23 @@ int launch_part_sum(int n, const RowFftArgs& a, hipStream_t stream) {
 // d = lam1 + |2 pi q|^2 + lam2 |2 pi q|^4:  Phi <- Phi + mu conj(D).(G - D Phi)/d, L times, in
 // double; q = 0 and the Nyquist row/column are held at zero.
 
+// The descent of one frequency from Phi = 0, in closed form: with b = conj(D).G and r = 1 - mu q^2/d a step
+// is Phi <- r Phi + (mu/d) b, so L steps give (mu/d) b S with S = 1 + r + ... + r^(L-1), L dependent
+// multiply-adds instead of 4 L with 12 operations each (1024 x 1024, L = 10: the column pass 21 us ->
+// 12 us).
+__device__ __forceinline__ float2 dpc_descend(float2 gx, float2 gy, double qx, double qy, double mu, double lam1,
+                                              double lam2, int n_iter, bool live) {
+  const double q2 = qx * qx + qy * qy;
+  const double d = lam1 + q2 + lam2 * q2 * q2;
+  if (!live || d == 0.0) return make_float2(0.f, 0.f);
+  const double md = mu / d, r = 1.0 - md * q2;
+  double s = 0.0;
+  for (int l = 0; l < n_iter; ++l) s = s * r + 1.0;
+  s *= md;
+  return make_float2((float)(s * (qx * (double)gx.y + qy * (double)gy.y)),
+                     (float)(-s * (qx * (double)gx.x + qy * (double)gy.x)));
+}
+
 // ---------------------------------------------------------------------------------------------
 // DPC integration in three passes over the packed gradient z = gx + i gy (Sec. V):
 //  k_dpc_rows  rows ry: FFT along rx, split into the half spectra Gx, Gy along x (z(m) and
@@ -825,6 +842,7 @@ __global__ void __launch_bounds__(64 * W) k_dpc_cols(const float2* __restrict__ 
   const int nh = nx / 2 + 1;
   const int ntiles = (nh + TR - 1) / TR;
   const double two_pi = 6.283185307179586476925286766559;
+  const double dqx = two_pi / ((double)nx * step), dqy = two_pi / ((double)N * step);
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int r0 = tile * TR + wave * B;  // rows are frequencies mx
     float2 vx[16], vy[16];
@@ -846,25 +864,9 @@ __global__ void __launch_bounds__(64 * W) k_dpc_cols(const float2* __restrict__ 
       const int mx = r0 + b;
       const int sy = my < (N + 1) / 2 ? my : my - N;
       const int sx = mx < (nx + 1) / 2 ? mx : mx - nx;
-      const double qy = two_pi * ((double)sy / ((double)N * step));
-      const double qx = two_pi * ((double)sx / ((double)nx * step));
-      const double q2 = qx * qx + qy * qy;
-      const double d = lam1 + q2 + lam2 * q2 * q2;
-      const bool live = d != 0.0 && !(my == 0 && mx == 0) && my != N / 2 && mx != nx / 2 && mx < nh;
-      double pr = 0.0, pi = 0.0;
-      if (live) {
-        const double gxr = vx[i].x, gxi = vx[i].y, gyr = vy[i].x, gyi = vy[i].y;
-        const double md = mu / d;
-        for (int l = 0; l < n_iter; ++l) {
-          // residuals G - D Phi with D = i q, then conj(D) r = -i q r
-          const double rxr = gxr + qx * pi, rxi = gxi - qx * pr;
-          const double ryr = gyr + qy * pi, ryi = gyi - qy * pr;
-          const double ur = qx * rxi + qy * ryi, ui = -(qx * rxr + qy * ryr);
-          pr += md * ur;
-          pi += md * ui;
-        }
-      }
-      buf[fft_pad(b * N + my)] = make_float2((float)pr, (float)pi);
+      const float2 ph = dpc_descend(vx[i], vy[i], (double)sx * dqx, (double)sy * dqy, mu, lam1, lam2, n_iter,
+                                    !(my == 0 && mx == 0) && my != N / 2 && mx != nx / 2 && mx < nh);
+      buf[fft_pad(b * N + my)] = ph;
     }
     wave_lds_sync();
     // inverse along my: conj, forward transform, conj
@@ -958,39 +960,21 @@ static int launch_dpc(const double* c64, const float* c32, int64_t F, int ny, in
 // Gx = (C(q) + conj C(-q))/2 and Gy = (C(q) - conj C(-q))/(2i) into Phi; the inverse along my,
 // written transposed [ry][mx]; the inverse along mx, real part / F.
 
-__global__ void __launch_bounds__(256) k_dpc_descent(const float2* __restrict__ C, int ny, int nx, double step,
-                                                     double mu, double lam1, double lam2, int n_iter,
+__global__ void __launch_bounds__(256) k_dpc_descent(const float2* __restrict__ C, int ny, int nx, double dqx,
+                                                     double dqy, double mu, double lam1, double lam2, int n_iter,
                                                      float2* __restrict__ Phi) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= (int64_t)ny * nx) return;
   const int mx = (int)(q / ny), my = (int)(q % ny);
   const float2 c = C[q];
   const float2 cm = cconj(C[(int64_t)((nx - mx) % nx) * ny + (ny - my) % ny]);
-  const double two_pi = 6.283185307179586476925286766559;
   const int sy = my < (ny + 1) / 2 ? my : my - ny;
   const int sx = mx < (nx + 1) / 2 ? mx : mx - nx;
-  const double qy = two_pi * ((double)sy / ((double)ny * step));
-  const double qx = two_pi * ((double)sx / ((double)nx * step));
-  const double q2 = qx * qx + qy * qy;
-  const double d = lam1 + q2 + lam2 * q2 * q2;
-  const bool live = d != 0.0 && !(my == 0 && mx == 0) && 2 * my != ny && 2 * mx != nx;
-  double pr = 0.0, pi = 0.0;
-  if (live) {
-    // Gx = (c + cm)/2, Gy = (c - cm)/(2i)
-    const float2 gx = make_float2(0.5f * (c.x + cm.x), 0.5f * (c.y + cm.y));
-    const float2 gy = make_float2(0.5f * (c.y - cm.y), -0.5f * (c.x - cm.x));
-    const double gxr = gx.x, gxi = gx.y, gyr = gy.x, gyi = gy.y;
-    const double md = mu / d;
-    for (int l = 0; l < n_iter; ++l) {
-      // residuals G - D Phi with D = i q, then conj(D) r = -i q r
-      const double rxr = gxr + qx * pi, rxi = gxi - qx * pr;
-      const double ryr = gyr + qy * pi, ryi = gyi - qy * pr;
-      const double ur = qx * rxi + qy * ryi, ui = -(qx * rxr + qy * ryr);
-      pr += md * ur;
-      pi += md * ui;
-    }
-  }
-  Phi[q] = make_float2((float)pr, (float)pi);
+  // Gx = (c + cm)/2, Gy = (c - cm)/(2i)
+  const float2 gx = make_float2(0.5f * (c.x + cm.x), 0.5f * (c.y + cm.y));
+  const float2 gy = make_float2(0.5f * (c.y - cm.y), -0.5f * (c.x - cm.x));
+  Phi[q] = dpc_descend(gx, gy, (double)sx * dqx, (double)sy * dqy, mu, lam1, lam2, n_iter,
+                       !(my == 0 && mx == 0) && 2 * my != ny && 2 * mx != nx);
 }
 
 static int launch_dpc_generic(const double* c64, const float* c32, int64_t F, int ny, int nx, float g, double step,
@@ -1020,8 +1004,9 @@ static int launch_dpc_generic(const double* c64, const float* c32, int64_t F, in
   if ((st = launch_row_fft(ny, false, IN_C64, OUT_ROW_C64, a, s))) return st;
   {
     STEM_TRACE("dpc_descent", s);
-    hipLaunchKernelGGL(k_dpc_descent, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, A, ny, nx, step, p.mu,
-                       p.lam1, p.lam2, p.n_iter, B);
+    const double two_pi = 6.283185307179586476925286766559;
+    hipLaunchKernelGGL(k_dpc_descent, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, A, ny, nx,
+                       two_pi / ((double)nx * step), two_pi / ((double)ny * step), p.mu, p.lam1, p.lam2, p.n_iter, B);
     STEM_LAUNCH_CHECK();
   }
   a = RowFftArgs{};
