@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(64 * kPrunedCols) k_psum(YArgs a, Optics o, in
 // follow one another), so a column's values are one contiguous stretch.  Each column is cut into
 // pieces of equal cost, cost = entries + kRunCost per run with entries (a run costs at least one
 // round whatever its length), the cost per piece Cc the same for every column (about total cost /
-// nws, see k_stream_cands); one wave sums one piece.  Every wave thus does about the same work (a column of few
+// nws, see k_stream_tables); one wave sums one piece.  Every wave thus does about the same work (a column of few
 // pairs is one short piece), and no wave leaves its column: its partial T is one row of ny values
 // at part + w ny, the pieces of column mx being the waves colseg[mx] .. colseg[mx + 1] - 1, which
 // the phase pass adds in order.
@@ -345,19 +345,15 @@ constexpr int64_t kRunCost = 192;
 // [E0, E1) of the array, and for the adjoint the whole runs [ra, rb) whose first entry lies in
 // [E0, E1) (the column's first piece from the column's first run, the last to its last, so that
 // the pieces of a column take each of its runs once, empty ones included).  Tables built at
-// FINALIZE: the column costs and spans by k_prune_runs, then k_stream_cands, k_stream_colseg and
-// k_stream_waves.
+// FINALIZE: the column costs and spans by k_prune_runs, then k_stream_tables and k_stream_waves.
 struct PieceTab {
   int64_t run, e0, e1, ra, rb;
 };
 
 // Table of the columns, ctab (int64): colseg [nx + 1], then the cost per piece, then per column
-// its cost and the span [first, last + 1) of its runs with entries (run indices), [nx][3], then
-// the candidate costs per piece and their piece counts [kStreamCands][2].
+// its cost and the span [first, last + 1) of its runs with entries (run indices), [nx][3].
 constexpr int kStreamCands = 256;
-__host__ __device__ inline size_t stream_ctab_words(int nx) {
-  return (size_t)(nx + 1) + 1 + 3 * (size_t)nx + 2 * kStreamCands;
-}
+__host__ __device__ inline size_t stream_ctab_words(int nx) { return (size_t)(nx + 1) + 1 + 3 * (size_t)nx; }
 
 template <bool CHI0>
 __global__ void __launch_bounds__(64 * kPrunedCols) k_psum_stream(YArgs a, Optics o, int ny, int nwmax,
@@ -431,122 +427,141 @@ __global__ void __launch_bounds__(64 * kPrunedCols) k_psum_stream(YArgs a, Optic
   if (lane == 0) a.wcnt[wid] = cc;
 }
 
-// The cost of the runs [r0, r0 + n) of the array (offsets poff): entries + kRunCost per non-empty run.
-__device__ __forceinline__ int64_t runs_cost(const int64_t* __restrict__ poff, int64_t r0, int n) {
-  int64_t c = 0;
-  for (int k = 0; k < n; ++k) {
-    const int64_t len = poff[r0 + k + 1] - poff[r0 + k];
-    c += len > 0 ? len + kRunCost : 0;
+// Inclusive scan of one value per thread over a workgroup of W waves (s: W entries of LDS); total, if
+// given, receives the sum.  It ends with a barrier.
+template <int W>
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* s, int64_t* total = nullptr) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t u = __shfl_up(v, o);
+    if (lane >= o) v += u;
   }
-  return c;
+  if (lane == 63) s[w] = v;
+  __syncthreads();
+  int64_t before = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < W; ++k) {
+    const int64_t x = s[k];
+    before += k < w ? x : 0;
+    all += x;
+  }
+  if (total) *total = all;
+  __syncthreads();
+  return v + before;
 }
 
-// The sum of the column costs, by every thread of a workgroup.
-__device__ __forceinline__ int64_t stream_total_cost(int nx, const int64_t* __restrict__ col, int64_t* s_sum) {
-  int64_t tot = 0;
-  for (int mx = threadIdx.x; mx < nx; mx += 256) tot += col[3 * mx];
-  s_sum[threadIdx.x] = tot;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) s_sum[threadIdx.x] += s_sum[threadIdx.x + off];
-    __syncthreads();
-  }
-  const int64_t total = s_sum[0];
-  __syncthreads();
-  return total;
-}
-
-// Candidate t (workgroup t of kStreamCands) for the cost per piece: lo + t (hi - lo) / (kStreamCands
-// - 1) over [lo, hi] = [total / nws, total / (nws - nx)] (the second always gives at most nws
-// pieces, as the pieces number at most total / Cc + nx), and its number of pieces.
-__global__ void __launch_bounds__(256) k_stream_cands(int nx, int nws, int64_t* __restrict__ ctab) {
-  __shared__ int64_t s_sum[256];
+// One workgroup, after k_prune_runs: the exclusive scan of the column totals (ptot: each column's first
+// entry; poff's last element: the number of entries), the cost per piece Cc and colseg, the exclusive scan
+// of the pieces per column ceil(cost / Cc).
+//
+// Cc is the smallest of kStreamCands candidates lo + t (hi - lo) / (kStreamCands - 1) over [lo, hi] =
+// [total / nws, total / (nws - nx)] whose pieces number at most nws, the waves the GPU holds at once (the
+// last always does, as the pieces number at most total / Cc + nx), so that each sums one piece.  The
+// number falls as Cc grows, so sixteen waves count for every sixteenth candidate first, then for the
+// sixteen up to the first that fits.  A column's cost is below 2^32 (n_k, Ny <= 4096): 32-bit divisions.
+// (The scan, a workgroup per candidate and the choice as three launches: 15 us and their gaps; a bisection
+// in 64 bits here 16 us; this 8 to 10 us.)
+constexpr int kTableThreads = 1024;
+__global__ void __launch_bounds__(kTableThreads) k_stream_tables(int n_k, int nx, int nws, int64_t* __restrict__ poff,
+                                                                 int64_t* __restrict__ ptot, int64_t pcap,
+                                                                 int64_t* __restrict__ ctab, int32_t* __restrict__ status) {
+  constexpr int T = kTableThreads, W = T / 64;
+  static_assert(kStreamCands == W * W, "two rounds of one candidate per wave");
+  __shared__ int64_t s[W];
+  __shared__ uint32_t s_cost[4096];
+  __shared__ int s_first;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t* col = ctab + (nx + 2);
-  const int64_t total = stream_total_cost(nx, col, s_sum);
+  // consecutive columns per thread, at most four (nx <= 4096)
+  const int per = (nx + T - 1) / T, m0 = t * per;
+  int64_t len[4], cost[4], sum = 0, csum = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool in = i < per && m0 + i < nx;
+    len[i] = in ? ptot[m0 + i] : 0;
+    cost[i] = in ? col[3 * (m0 + i)] : 0;
+    sum += len[i];
+    csum += cost[i];
+    if (in) s_cost[m0 + i] = (uint32_t)cost[i];
+  }
+  int64_t entries, total;
+  int64_t base = block_scan<W>(sum, s, &entries) - sum;
+  block_scan<W>(csum, s, &total);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (i < per && m0 + i < nx) ptot[m0 + i] = base;
+    base += len[i];
+  }
+  if (t == 0) {
+    poff[(int64_t)nx * n_k] = entries;
+    if (entries > pcap) report(status, STEM_EWORKSPACE);  // never with the layout's bound
+  }
   const int64_t lo = total > 0 ? (total + nws - 1) / nws : 1;
   const int64_t hi = total <= 0 ? 1 : nws > nx ? (total + (nws - nx) - 1) / (nws - nx) : total;
-  const int64_t c = hi > lo ? lo + (int64_t)blockIdx.x * (hi - lo) / (kStreamCands - 1) : hi;
-  int64_t n = 0;
-  for (int mx = threadIdx.x; mx < nx; mx += 256) n += (col[3 * mx] + c - 1) / c;
-  s_sum[threadIdx.x] = n;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) s_sum[threadIdx.x] += s_sum[threadIdx.x + off];
+  auto cand = [&](int i) { return hi > lo ? lo + (int64_t)i * (hi - lo) / (kStreamCands - 1) : hi; };
+  auto pieces = [&](uint32_t cost, int64_t c) -> uint32_t {
+    return cost == 0 ? 0u : c >= (int64_t)cost ? 1u : (cost - 1) / (uint32_t)c + 1u;
+  };
+  // the first candidate of first, first + step, ... (one per wave) that fits, else the last
+  auto choose = [&](int first, int step) {
+    const int64_t c = cand(first + wave * step);
+    uint32_t n = 0;
+    for (int mx = lane; mx < nx; mx += 64) n += pieces(s_cost[mx], c);
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+    if (t == 0) s_first = W - 1;
     __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    int64_t* cand = ctab + (nx + 2) + 3 * (int64_t)nx;
-    cand[2 * blockIdx.x] = c;
-    cand[2 * blockIdx.x + 1] = s_sum[0];
-  }
-}
-
-// One workgroup: the cost per piece Cc, the smallest candidate whose pieces number at most nws (the
-// last candidate always does), so that the launch's nws waves (the waves the GPU holds at once)
-// each sum one piece and every compute unit gets the same work; then colseg, the exclusive scan of
-// the pieces per column ceil(cost / Cc).
-__global__ void __launch_bounds__(256) k_stream_colseg(int nx, int nws, int64_t* __restrict__ ctab) {
-  __shared__ int64_t s_sum[256];
-  const int64_t* col = ctab + (nx + 2);
-  const int64_t* cand = col + 3 * (int64_t)nx;
-  static_assert(kStreamCands == 256, "one candidate per thread");
-  const int t = threadIdx.x;
-  s_sum[t] = cand[2 * t + 1] <= nws || t == kStreamCands - 1 ? cand[2 * t] : INT64_MAX;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (t < off) s_sum[t] = min(s_sum[t], s_sum[t + off]);
+    if (lane == 0 && (int64_t)n <= nws) atomicMin(&s_first, wave);
     __syncthreads();
-  }
-  const int64_t Cc = s_sum[0];
-  __syncthreads();
-  const int per = (nx + 255) / 256, m0 = t * per;
-  int64_t n = 0;
-  for (int mx = m0; mx < m0 + per && mx < nx; ++mx) n += (col[3 * mx] + Cc - 1) / Cc;
-  s_sum[t] = n;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int64_t v = t >= off ? s_sum[t - off] : 0;
+    const int f = s_first;
     __syncthreads();
-    s_sum[t] += v;
-    __syncthreads();
+    return first + f * step;
+  };
+  const int top = choose(W - 1, W);
+  const int a = choose(top - (W - 1), 1);
+  const int64_t Cc = cand(a);
+  int64_t all;
+  int64_t mine = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mine += pieces((uint32_t)cost[i], Cc);
+  int64_t seg = block_scan<W>(mine, s, &all) - mine;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (i < per && m0 + i < nx) ctab[m0 + i] = seg;
+    seg += pieces((uint32_t)cost[i], Cc);
   }
-  int64_t base = s_sum[t] - n;
-  for (int mx = m0; mx < m0 + per && mx < nx; ++mx) {
-    ctab[mx] = base;
-    base += (col[3 * mx] + Cc - 1) / Cc;
-  }
-  if (t == 255) {
-    ctab[nx] = s_sum[255];
+  if (t == 0) {
+    ctab[nx] = all;
     ctab[nx + 1] = Cc;
   }
 }
 
-// Per column (workgroup): the pieces' first runs, entry ranges and (after a barrier) run ranges.  Piece p of column mx starts at
-// cost p Cc of the column; inside run r (cost [c_r, c_r + kRunCost + len)) that is entry
-// max(0, p Cc - c_r - kRunCost) of the run.  Piece p ends where piece p + 1 starts, the last at
-// the column's end.
-__global__ void __launch_bounds__(256) k_stream_waves(int n_k, const int64_t* __restrict__ poff, int nx,
+// Per column (workgroup): its offsets made absolute, then the pieces' first runs, entry ranges and (after a
+// barrier) run ranges.  Piece p of column mx starts at cost p Cc of the column; inside run r (cost [c_r, c_r +
+// kRunCost + len)) that is entry max(0, p Cc - c_r - kRunCost) of the run.  Piece p ends where piece p + 1
+// starts, the last at the column's end.
+__global__ void __launch_bounds__(256) k_stream_waves(int n_k, int64_t* __restrict__ poff,
+                                                      const int64_t* __restrict__ ptot, int nx,
                                                       const int64_t* __restrict__ ctab, PieceTab* __restrict__ wtab) {
-  __shared__ int64_t s_pre[256];
+  __shared__ int64_t s[4];
   const int mx = blockIdx.x;
   const int64_t* col = ctab + (nx + 2) + 3 * (int64_t)mx;
   const int64_t ccost = col[0], Cc = ctab[nx + 1], seg0 = ctab[mx];
+  const int64_t base = ptot[mx], ce = mx + 1 < nx ? ptot[mx + 1] : poff[(int64_t)nx * n_k];
+  const int64_t r0 = (int64_t)mx * n_k;
+  for (int kd = threadIdx.x; kd < n_k; kd += 256) poff[r0 + kd] += base;
   if (ccost == 0) return;
+  __syncthreads();
   const int64_t npieces = (ccost + Cc - 1) / Cc;
   const int q = (n_k + 255) / 256, k0 = min((int)threadIdx.x * q, n_k), k1 = min(k0 + q, n_k);
-  const int64_t r0 = (int64_t)mx * n_k;
-  const int64_t mine = runs_cost(poff, r0 + k0, k1 - k0);
-  s_pre[threadIdx.x] = mine;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int64_t v = threadIdx.x >= off ? s_pre[threadIdx.x - off] : 0;
-    __syncthreads();
-    s_pre[threadIdx.x] += v;
-    __syncthreads();
-  }
-  int64_t cr = s_pre[threadIdx.x] - mine;  // cost before this thread's first run
+  auto end_of = [&](int kd) { return kd + 1 < n_k ? poff[r0 + kd + 1] : ce; };
+  int64_t mine = 0;  // cost of this thread's runs: entries + kRunCost per run with entries
   for (int kd = k0; kd < k1; ++kd) {
-    const int64_t e0 = poff[r0 + kd], len = poff[r0 + kd + 1] - e0;
+    const int64_t len = end_of(kd) - poff[r0 + kd];
+    mine += len > 0 ? len + kRunCost : 0;
+  }
+  int64_t cr = block_scan<4>(mine, s) - mine;  // cost before this thread's first run
+  for (int kd = k0; kd < k1; ++kd) {
+    const int64_t e0 = poff[r0 + kd], len = end_of(kd) - e0;
     if (len <= 0) continue;
     const int64_t c1 = cr + kRunCost + len;
     // the pieces starting inside this run's cost range [cr, c1)
@@ -558,10 +573,7 @@ __global__ void __launch_bounds__(256) k_stream_waves(int n_k, const int64_t* __
     }
     cr = c1;
   }
-  if (threadIdx.x == 255) {
-    const int64_t ce = mx + 1 < nx ? poff[r0 + n_k] : poff[(int64_t)nx * n_k];
-    wtab[seg0 + npieces - 1].e1 = ce;
-  }
+  if (threadIdx.x == 255) wtab[seg0 + npieces - 1].e1 = ce;
   __syncthreads();
   // the adjoint's run ranges: piece p takes the runs whose first entry lies in its entries (the
   // first piece from the column's first run, the last to its last run)
