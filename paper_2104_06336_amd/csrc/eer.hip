@@ -40,9 +40,28 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ id
   for (int64_t f = tid; f < n_frames; f += nthr)
     if (off[frame0 + f + 1] < off[frame0 + f]) bits |= STEM_EOFFSETS;
   if (bounds_ok) {
-    for (int64_t e = e0 + tid; e < e1; e += nthr) {
-      const int32_t k = idx[e];
-      if (k < 0 || k >= npix) bits |= STEM_ERANGE;
+    // whole 16-byte lines that hold at least one of the events (the others of a line are masked), four in
+    // flight per thread
+    const int sh = (int)((((uintptr_t)(idx + e0)) & 15) >> 2);
+    const int64_t al = e0 - sh, ng = (e1 - al + 3) >> 2;
+    for (int64_t g0 = tid; g0 < ng; g0 += 4 * nthr) {
+      int4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t g = g0 + u * nthr;
+        v[u] = g < ng ? *(const int4*)(idx + al + 4 * g) : make_int4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t e = al + 4 * (g0 + u * nthr);
+        const bool bad[4] = {(uint32_t)v[u].x >= (uint32_t)npix, (uint32_t)v[u].y >= (uint32_t)npix,
+                             (uint32_t)v[u].z >= (uint32_t)npix, (uint32_t)v[u].w >= (uint32_t)npix};
+        if (bad[0] | bad[1] | bad[2] | bad[3]) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (bad[q] && e + q >= e0 && e + q < e1) bits |= STEM_ERANGE;
+        }
+      }
     }
   }
   int32_t wbits = bits;
@@ -69,27 +88,6 @@ __device__ __forceinline__ bool load_rel_offsets(const int64_t* __restrict__ off
 }
 
 // ---------------------------------------------------------------------------------------------
-// Group c of four events starting at the absolute index e (16-byte aligned): k[j] = idx[e + j],
-// ok[j] = e + j in [a0, aend); the whole group is one 16-byte load when it lies inside.
-__device__ __forceinline__ void load_group(const int32_t* __restrict__ idx, int64_t e, int64_t a0, int64_t aend,
-                                           int32_t* k, bool* ok) {
-  if (e >= a0 && e + 4 <= aend) {
-    const int4 v = *(const int4*)(idx + e);
-    k[0] = v.x;
-    k[1] = v.y;
-    k[2] = v.z;
-    k[3] = v.w;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ok[j] = true;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      ok[j] = e + j >= a0 && e + j < aend;
-      k[j] = ok[j] ? idx[e + j] : 0;
-    }
-  }
-}
-
 // Staging of a workgroup's events in LDS: the events [a0, a0 + n) (absolute indices, n <= kComWin)
 // are copied as whole 16-byte lines from the aligned position at or below a0; s[sh + j] then holds
 // event a0 + j (sh < 4 is returned).  Every line holds at least one of the events, so it lies in
@@ -125,9 +123,10 @@ __device__ __forceinline__ int stage_events(const int32_t* __restrict__ idx, int
 
 constexpr int kComFrames = 256;
 
+template <bool D24>
 __global__ void __launch_bounds__(kComThreads) k_com(const int32_t* __restrict__ idx,
                                                      const int64_t* __restrict__ off,
-                                                     int64_t frame0, int64_t n_frames, Magic divw,
+                                                     int64_t frame0, int64_t n_frames, PixDiv div,
                                                      int32_t cx, int32_t cy, int32_t npix,
                                                      int64_t nplane, double* __restrict__ com64,
                                                      float* __restrict__ com32,
@@ -153,16 +152,19 @@ __global__ void __launch_bounds__(kComThreads) k_com(const int32_t* __restrict__
     __syncthreads();
     const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
     const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
-    int32_t ax[4] = {0, 0, 0, 0}, ay[4] = {0, 0, 0, 0};
-    uint32_t nbad = 0;
-    // out-of-range indices are counted (and reported) and contribute nothing; no branches
+    // out-of-range indices are counted (and reported) and contribute nothing; no branches.  With the rows
+    // ky of the indices k, the columns' sum is the sum of k less W times the sum of ky, here modulo
+    // 2^32: a window's columns and rows sum to less (kComWin W, kComWin H < 2^32 for sides below 2^18;
+    // larger ones sum in 64 bits).
+    using S = std::conditional_t<D24, uint32_t, uint64_t>;
+    S sk[4] = {0, 0, 0, 0}, sr[4] = {0, 0, 0, 0};
+    uint32_t nin = 0;
     auto add = [&](int j, int32_t k) {
       const bool in = (uint32_t)k < (uint32_t)npix;
-      nbad += in ? 0u : 1u;
+      nin += in ? 1u : 0u;
       const uint32_t kk = in ? (uint32_t)k : 0u;
-      const uint32_t ky = magic_div(kk, divw);
-      ax[j] += in ? (int32_t)(kk - ky * divw.d) - cx : 0;
-      ay[j] += in ? (int32_t)ky - cy : 0;
+      sk[j] += kk;
+      sr[j] += pix_row<D24>(kk, div);
     };
     int e = lo;
     for (; e + 4 <= hi; e += 4) {
@@ -170,9 +172,11 @@ __global__ void __launch_bounds__(kComThreads) k_com(const int32_t* __restrict__
       for (int j = 0; j < 4; ++j) add(j, s_ev[e + j]);
     }
     for (; e < hi; ++e) add(0, s_ev[e]);
-    if (nbad) bad = STEM_ERANGE;
-    sx += (int64_t)ax[0] + ax[1] + ax[2] + ax[3];
-    sy += (int64_t)ay[0] + ay[1] + ay[2] + ay[3];
+    if (lo < hi && nin != (uint32_t)(hi - lo)) bad = STEM_ERANGE;
+    const S tk = (sk[0] + sk[1]) + (sk[2] + sk[3]), tr = (sr[0] + sr[1]) + (sr[2] + sr[3]);
+    const S tc = tk - tr * (S)div.mg.d;
+    sx += (int64_t)tc - (int64_t)cx * nin;
+    sy += (int64_t)tr - (int64_t)cy * nin;
   }
   if (t < nf) {
     const int64_t fr = fb + t;
@@ -198,9 +202,10 @@ int launch_com(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
   if (n_frames == 0) return STEM_OK;
   const int64_t blocks = (n_frames + kComFrames - 1) / kComFrames;
   STEM_TRACE("com_moments", stream);
-  hipLaunchKernelGGL(k_com, dim3((unsigned)blocks), dim3(kComThreads), 0, stream, idx, off, frame0,
-                     n_frames, make_magic((uint32_t)det.W), det.cx, det.cy, det.W * det.H, nplane,
-                     com64, com32, counts, status);
+  const PixDiv div = make_pixdiv(det.W, det.H, 1);
+  const auto fn = div.d24 ? k_com<true> : k_com<false>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kComThreads), 0, stream, idx, off, frame0, n_frames, div,
+                     det.cx, det.cy, det.W * det.H, nplane, com64, com32, counts, status);
   STEM_LAUNCH_CHECK();
   return STEM_OK;
 }
@@ -209,14 +214,19 @@ int launch_com(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
 // virtual annular detectors: the same staging as k_com; thread t counts the events of frame t in
 // each annulus [lo_j, hi_j) of squared pixel distance (exact int64 thresholds)
 
+//
+// D24 (sides below 2^15 and the zero-frequency pixel on the detector, so d^2 < 2^32): the squared distance by
+// 24-bit multiplications and one unsigned comparison per annulus.
+
 struct Annuli {
   int64_t lo[STEM_MAX_ANNULI], hi[STEM_MAX_ANNULI];
+  uint32_t lo32[STEM_MAX_ANNULI], len32[STEM_MAX_ANNULI];  // lo and hi - lo, cut at 2^32 - 1
 };
 
-template <int NA>
+template <int NA, bool D24>
 __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restrict__ idx,
                                                          const int64_t* __restrict__ off, int64_t frame0,
-                                                         int64_t n_frames, Magic divw, int32_t cx, int32_t cy,
+                                                         int64_t n_frames, PixDiv div, int32_t cx, int32_t cy,
                                                          int32_t npix, Annuli an, int64_t F,
                                                          int32_t* __restrict__ out, int32_t* status) {
   __shared__ __align__(16) int32_t s_ev[kComWin + 8];
@@ -241,17 +251,32 @@ __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restri
     __syncthreads();
     const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
     const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
-    for (int e = lo; e < hi; ++e) {
-      const int32_t k = s_ev[e];
+    auto add = [&](int32_t k) {
       const bool in = (uint32_t)k < (uint32_t)npix;
       nbad += in ? 0u : 1u;
       const uint32_t kk = in ? (uint32_t)k : 0u;
-      const uint32_t ky = magic_div(kk, divw);
-      const int64_t dx = (int64_t)(kk - ky * divw.d) - cx, dy = (int64_t)ky - cy;
-      const int64_t d2 = dx * dx + dy * dy;
+      const uint32_t ky = pix_row<D24>(kk, div), kx = pix_col<D24>(kk, ky, div);
+      if constexpr (D24) {
+        const int dx = (int)kx - cx, dy = (int)ky - cy;
+        const uint32_t d2 = (uint32_t)__mul24(dx, dx) + (uint32_t)__mul24(dy, dy);
 #pragma unroll
-      for (int j = 0; j < NA; ++j) cnt[j] += (in && d2 >= an.lo[j] && d2 < an.hi[j]) ? 1 : 0;
+        for (int j = 0; j < NA; ++j) cnt[j] += (in && d2 - an.lo32[j] < an.len32[j]) ? 1 : 0;
+      } else {
+        const int64_t dx = (int64_t)kx - cx, dy = (int64_t)ky - cy;
+        const int64_t d2 = dx * dx + dy * dy;
+#pragma unroll
+        for (int j = 0; j < NA; ++j) cnt[j] += (in && d2 >= an.lo[j] && d2 < an.hi[j]) ? 1 : 0;
+      }
+    };
+    int e = lo;
+    for (; e + 4 <= hi; e += 4) {
+      int32_t k[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) k[j] = s_ev[e + j];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) add(k[j]);
     }
+    for (; e < hi; ++e) add(s_ev[e]);
   }
   if (t < nf) {
 #pragma unroll
@@ -264,23 +289,33 @@ __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restri
 // sum of frames: the event range is split evenly over the workgroups; each counts its events into
 // 32-bit LDS counters over a box of up to 128 x 128 pixels around the zero-frequency pixel, where
 // the bright-field disk and nearly all events fall (events outside the box go straight to global
-// atomics), then adds the box to the global sum once.
+// atomics: kept in LDS until the box's turn they took 117 us in all, they overlap the events' loads here),
+// then adds the box to the global sum once.
+//
+// Bound by those global atomics: every workgroup adds the whole disk.  So one large workgroup per compute unit
+// (256 of 1024 threads), two counters per 64-bit atomic where the sum is aligned for it (a counter stays
+// below 2^32), and every workgroup starts its box at another place, so that they do not queue at the
+// same lines.  Measured at 4.2e7 events in 2^20 frames (4% outside the disk): 165 us with 512 workgroups of
+// 256 threads, 32-bit atomics and one order, 103 us now.
 
 constexpr int kSumBox = 128;
-constexpr int kSumBlocks = 512;
+constexpr int kSumBlocks = 256;
+constexpr int kSumThreads = 1024;
 
-__global__ void __launch_bounds__(256) k_sum_events(const int32_t* __restrict__ idx, const int64_t* __restrict__ off,
-                                                    int64_t frame0, int64_t n_frames, Magic divw, int32_t npix,
-                                                    int32_t bx0, int32_t by0, int32_t bw, int32_t bh,
-                                                    uint32_t* __restrict__ sum, int32_t* status) {
-  __shared__ uint32_t s_box[kSumBox * kSumBox];
+template <bool D24, bool PAIR>
+__global__ void __launch_bounds__(kSumThreads) k_sum_events(const int32_t* __restrict__ idx,
+                                                            const int64_t* __restrict__ off, int64_t frame0,
+                                                            int64_t n_frames, PixDiv div, int32_t npix, int32_t bx0,
+                                                            int32_t by0, int32_t bw, int32_t bh,
+                                                            uint32_t* __restrict__ sum, int32_t* status) {
+  __shared__ __align__(8) uint32_t s_box[kSumBox * kSumBox];
   const int64_t e0 = off[frame0], e1 = off[frame0 + n_frames];
   if (e1 < e0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) report(status, STEM_EOFFSETS);
     return;
   }
   const int nbox = bw * bh;
-  for (int i = threadIdx.x; i < nbox; i += blockDim.x) s_box[i] = 0u;
+  for (int i = threadIdx.x; i < nbox; i += kSumThreads) s_box[i] = 0u;
   __syncthreads();
   // this workgroup's share of the events, in whole 16-byte groups where possible
   const int64_t per = ((e1 - e0 + gridDim.x - 1) / gridDim.x + 3) & ~3ll;
@@ -291,45 +326,63 @@ __global__ void __launch_bounds__(256) k_sum_events(const int32_t* __restrict__ 
     const int sh = (int)((((uintptr_t)(idx + a0)) & 15) >> 2);
     const int64_t al = a0 - sh;
     const int64_t ng = (aend - al + 3) >> 2;
-    constexpr int U = 4;  // groups per thread in flight
-    for (int64_t g0 = threadIdx.x; g0 < ng; g0 += (int64_t)U * blockDim.x) {
-      int32_t k[U][4];
-      bool ok[U][4];
+    auto add = [&](int32_t k, bool ok) {
+      const bool in = ok && (uint32_t)k < (uint32_t)npix;
+      nbad += ok && !in ? 1u : 0u;
+      const uint32_t ky = pix_row<D24>((uint32_t)k, div);
+      const int x = (int)pix_col<D24>((uint32_t)k, ky, div) - bx0, y = (int)ky - by0;
+      const bool box = (uint32_t)x < (uint32_t)bw && (uint32_t)y < (uint32_t)bh;
+      if (in && box) atomicAdd(&s_box[y * bw + x], 1u);
+      else if (in) atomicAdd(&sum[k], 1u);
+    };
+    // whole 16-byte lines that hold at least one of the events (the others of the first and last line are
+    // masked), U of them in flight per thread while the U before are counted
+    constexpr int U = 4;
+    int4 v[U];
+    auto load = [&](int64_t g0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int64_t g = g0 + (int64_t)u * blockDim.x;
-        if (g < ng) {
-          load_group(idx, al + 4 * g, a0, aend, k[u], ok[u]);
-        } else {
+        const int64_t g = g0 + u * kSumThreads;
+        v[u] = *(const int4*)(idx + al + 4 * (g < ng ? g : ng - 1));
+      }
+    };
+    load(threadIdx.x);
+    for (int64_t g0 = threadIdx.x; g0 < ng; g0 += U * kSumThreads) {
+      int4 c[U];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            ok[u][q] = false;
-            k[u][q] = 0;
-          }
+      for (int u = 0; u < U; ++u) c[u] = v[u];
+      load(g0 + U * kSumThreads);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t g = g0 + u * kSumThreads;
+        if (g > 0 && g < ng - 1) {
+          add(c[u].x, true);
+          add(c[u].y, true);
+          add(c[u].z, true);
+          add(c[u].w, true);
+        } else if (g < ng) {
+          const int64_t e = al + 4 * g;
+          add(c[u].x, e >= a0 && e < aend);
+          add(c[u].y, e + 1 >= a0 && e + 1 < aend);
+          add(c[u].z, e + 2 >= a0 && e + 2 < aend);
+          add(c[u].w, e + 3 >= a0 && e + 3 < aend);
         }
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!ok[u][q]) continue;
-          if ((uint32_t)k[u][q] >= (uint32_t)npix) {
-            ++nbad;
-            continue;
-          }
-          const uint32_t ky = magic_div((uint32_t)k[u][q], divw);
-          const int x = (int)((uint32_t)k[u][q] - ky * divw.d) - bx0, y = (int)ky - by0;
-          if ((uint32_t)x < (uint32_t)bw && (uint32_t)y < (uint32_t)bh)
-            atomicAdd(&s_box[y * bw + x], 1u);
-          else
-            atomicAdd(&sum[k[u][q]], 1u);
-        }
     }
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < nbox; p += blockDim.x) {
-    const uint32_t c = s_box[p];
-    if (c) atomicAdd(&sum[(int64_t)(by0 + p / bw) * divw.d + bx0 + p % bw], c);
+  constexpr int P = PAIR ? 2 : 1;
+  const int n = nbox / P, start = (int)((int64_t)n * blockIdx.x / gridDim.x);
+  for (int i = threadIdx.x; i < n; i += kSumThreads) {
+    const int p = P * (i + start < n ? i + start : i + start - n);
+    uint32_t* dst = sum + (int64_t)(by0 + p / bw) * div.mg.d + bx0 + p % bw;
+    if constexpr (PAIR) {
+      const unsigned long long c = *(const unsigned long long*)&s_box[p];
+      if (c) atomicAdd((unsigned long long*)dst, c);
+    } else {
+      const uint32_t c = s_box[p];
+      if (c) atomicAdd(dst, c);
+    }
   }
   if (nbad) report(status, STEM_ERANGE);
 }
@@ -506,9 +559,8 @@ struct BinShape {
 // global per-pixel table.
 constexpr int kBoxRows = 64;  // bin rows of the largest box whose row runs travel as arguments
 struct BinBox {
-  Magic mw;           // division by the detector width W
-  uint32_t mbin;      // ceil(2^32 / bin); 0 for bin = 1
-  int32_t W, bin;
+  PixDiv div;         // division by the detector width W and by the binning
+  int32_t bin;
   int32_t bx0, by0, bw, bh;
   int32_t start[kBoxRows], lo[kBoxRows], hi[kBoxRows];  // row runs of the box's rows (BOX)
 };
@@ -547,7 +599,7 @@ __device__ __forceinline__ void seg_step(int key, int32_t& ax, int32_t& ay) {
 // BOX: the first nset workgroups bin nothing; the first writes the geometry, the others the interval table
 // and the mask (with B >= 4 columns a set, one word per workgroup and every fourth column per wave, else
 // one word per wave), beside the binning's rather than before it.
-template <typename DT, bool BOX, bool COM, int FR>
+template <typename DT, bool BOX, bool COM, int FR, bool D24>
 __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__ idx,
                                                      const int64_t* __restrict__ off, int64_t frame0,
                                                      int64_t n_frames, int32_t npix,
@@ -724,9 +776,9 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
             const uint32_t kk = ok && in ? (uint32_t)k : 0u;  // 32-bit offset from the table base
             int v;
             if constexpr (BOX) {
-              const uint32_t ky = magic_div(kk, box.mw), kx = kk - ky * (uint32_t)box.W;
-              const uint32_t rx = (box.mbin ? __umulhi(kx, box.mbin) : kx) - (uint32_t)box.bx0;
-              const uint32_t ry = (box.mbin ? __umulhi(ky, box.mbin) : ky) - (uint32_t)box.by0;
+              const uint32_t ky = pix_row<D24>(kk, box.div), kx = pix_col<D24>(kk, ky, box.div);
+              const uint32_t rx = pix_bin<D24>(kx, box.div) - (uint32_t)box.bx0;
+              const uint32_t ry = pix_bin<D24>(ky, box.div) - (uint32_t)box.by0;
               v = rx < (uint32_t)box.bw && ry < (uint32_t)box.bh ? (int)s_box[ry * box.bw + rx] : -1;
             } else {
               v = (int)*(const int16_t*)((const char*)lut + 2u * kk);
@@ -757,7 +809,7 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(const int32_t* __restrict__
                 }
                 // an index outside the detector adds nothing (it is reported by the binning)
                 if ((uint32_t)k < (uint32_t)npix) {
-                  const uint32_t ky = magic_div((uint32_t)k, box.mw), kx = (uint32_t)k - ky * (uint32_t)box.W;
+                  const uint32_t ky = pix_row<D24>((uint32_t)k, box.div), kx = pix_col<D24>((uint32_t)k, ky, box.div);
                   ax += (int32_t)kx - com.cx;
                   ay += (int32_t)ky - com.cy;
                 }
@@ -896,10 +948,8 @@ static bool make_box(const stem_det& det, double r2, BinBox& box) {
     }
     run_start += hi - lo;
   }
-  box.W = det.W;
   box.bin = det.bin;
-  box.mw = make_magic((uint32_t)det.W);
-  box.mbin = det.bin == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + det.bin - 1) / det.bin);
+  box.div = make_pixdiv(det.W, det.H, det.bin);
   box.bx0 = bxa;
   box.by0 = bya;
   box.bw = bxb > bxa ? bxb - bxa : 0;
@@ -964,9 +1014,10 @@ int launch_bin(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
   auto launch = [&](auto dt, auto bx, auto cm, auto frames) {
     using DT = decltype(dt);
     constexpr bool BX = decltype(bx)::value, CM = decltype(cm)::value;
-    hipLaunchKernelGGL((k_bin<DT, BX, CM, decltype(frames)::value>), grid, dim3(kBinThreads), BX ? lds : 0, stream, idx,
-                       off, frame0, n_frames, npix, lut, rows, box, n_k, F, (DT*)D, co, geo, sj, nset, fblocks,
-                       status);
+    constexpr int FR = decltype(frames)::value;
+    const auto fn = box.div.d24 ? k_bin<DT, BX, CM, FR, true> : k_bin<DT, BX, CM, FR, false>;
+    hipLaunchKernelGGL(fn, grid, dim3(kBinThreads), BX ? lds : 0, stream, idx, off, frame0, n_frames, npix, lut, rows,
+                       box, n_k, F, (DT*)D, co, geo, sj, nset, fblocks, status);
   };
   auto go = [&](auto dt, auto bx, auto cm) {
     if (fr == 128) launch(dt, bx, cm, std::integral_constant<int, 128>{});
@@ -1064,25 +1115,27 @@ extern "C" int virtual_annular(const int32_t* d_idx, const int64_t* d_off, int64
   if (n_frames == 0) return STEM_OK;
   hipStream_t s = (hipStream_t)stream_;
   const int64_t blocks = (n_frames + kComFrames - 1) / kComFrames;
-  const Magic mw = make_magic((uint32_t)det->W);
+  for (int j = 0; j < STEM_MAX_ANNULI; ++j) {
+    const int64_t top = 0xffffffffll, lo = an.lo[j] < top ? an.lo[j] : top, hi = an.hi[j] < top ? an.hi[j] : top;
+    an.lo32[j] = (uint32_t)lo;
+    an.len32[j] = hi > lo ? (uint32_t)(hi - lo) : 0u;
+  }
+  const PixDiv div = make_pixdiv(det->W, det->H, 1);
+  const bool d24 = div.d24 && det->cx >= 0 && det->cx <= det->W && det->cy >= 0 && det->cy <= det->H;
   STEM_TRACE("virtual_annular", s);
   const dim3 grid((unsigned)blocks), blk(kComThreads);
   const int npix = det->W * det->H;
-  if (n_det <= 1)
-    hipLaunchKernelGGL(k_annular<1>, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, mw, det->cx, det->cy, npix, an,
-                       F, d_out, d_status);
-  else if (n_det <= 2)
-    hipLaunchKernelGGL(k_annular<2>, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, mw, det->cx, det->cy, npix, an,
-                       F, d_out, d_status);
-  else if (n_det <= 4)
-    hipLaunchKernelGGL(k_annular<4>, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, mw, det->cx, det->cy, npix, an,
-                       F, d_out, d_status);
-  else if (n_det <= 8)
-    hipLaunchKernelGGL(k_annular<8>, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, mw, det->cx, det->cy, npix, an,
-                       F, d_out, d_status);
-  else
-    hipLaunchKernelGGL(k_annular<16>, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, mw, det->cx, det->cy, npix,
-                       an, F, d_out, d_status);
+  auto go = [&](auto na) {
+    constexpr int NA = decltype(na)::value;
+    const auto fn = d24 ? k_annular<NA, true> : k_annular<NA, false>;
+    hipLaunchKernelGGL(fn, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, div, det->cx, det->cy, npix, an, F, d_out,
+                       d_status);
+  };
+  if (n_det <= 1) go(std::integral_constant<int, 1>{});
+  else if (n_det <= 2) go(std::integral_constant<int, 2>{});
+  else if (n_det <= 4) go(std::integral_constant<int, 4>{});
+  else if (n_det <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 16>{});
   STEM_LAUNCH_CHECK();
   return STEM_OK;
 }
@@ -1099,8 +1152,13 @@ extern "C" int sum_frames(const int32_t* d_idx, const int64_t* d_off, int64_t fr
   by0 = by0 < 0 ? 0 : (by0 > H - bh ? H - bh : by0);
   {
     STEM_TRACE("sum_frames", s);
-    hipLaunchKernelGGL(k_sum_events, dim3(kSumBlocks), dim3(256), 0, s, d_idx, d_off, frame0, n_frames,
-                       make_magic((uint32_t)W), W * H, bx0, by0, bw, bh, d_sum, d_status);
+    const PixDiv div = make_pixdiv(W, H, 1);
+    // pairs of counters: even rows of the sum and of the box, from an 8-byte boundary
+    const bool pair = ((uintptr_t)d_sum & 7) == 0 && W % 2 == 0 && bx0 % 2 == 0 && bw % 2 == 0;
+    const auto fn = div.d24 ? (pair ? k_sum_events<true, true> : k_sum_events<true, false>)
+                            : (pair ? k_sum_events<false, true> : k_sum_events<false, false>);
+    hipLaunchKernelGGL(fn, dim3(kSumBlocks), dim3(kSumThreads), 0, s, d_idx, d_off, frame0, n_frames, div, W * H, bx0,
+                       by0, bw, bh, d_sum, d_status);
     STEM_LAUNCH_CHECK();
   }
   if (d_mean) {

@@ -30,6 +30,51 @@ __host__ __device__ __forceinline__ uint32_t magic_div(uint32_t n, const Magic& 
   return (uint32_t)(((uint64_t)n * mg.m) >> mg.shift);
 }
 
+// Row of a detector pixel, k div W.  Detectors of up to 2^24 pixels take one full-rate 24-bit
+// multiply (D24): ((k << sh) m) >> 32 with m = ceil(2^(32-sh) / W) < 2^24, exact while k (m W - 2^(32-sh)) <
+// 2^(32-sh) for every pixel.  Others multiply in 64 bits.  mbin: division of a coordinate by the binning,
+// ((x << 8) mbin) >> 32 with mbin = ceil(2^24 / bin) (D24, exact while x bin < 2^24), else (x mbin) >> 32 with
+// ceil(2^32 / bin); 0 for bin = 1.
+struct PixDiv {
+  Magic mg;
+  uint32_t m, sh, mbin, d24;
+};
+
+inline PixDiv make_pixdiv(int32_t W, int32_t H, int32_t bin) {
+  PixDiv p{make_magic((uint32_t)W), 0u, 0u, 0u, 0u};
+  const uint64_t npix = (uint64_t)W * (uint64_t)H;
+  for (uint32_t sh = 0; sh <= 8 && (npix << sh) <= (1ull << 24) && W < 32768 && H < 32768; ++sh) {
+    const uint64_t one = 1ull << (32 - sh), m = (one + W - 1) / W;
+    if (m >= (1ull << 24) || (npix - 1) * (m * W - one) >= one) continue;
+    if ((uint64_t)(W > H ? W : H) * (uint64_t)bin >= (1ull << 24)) break;
+    p.m = (uint32_t)m;
+    p.sh = sh;
+    p.d24 = 1u;
+    break;
+  }
+  if (bin > 1) p.mbin = p.d24 ? (uint32_t)(((1ull << 24) + bin - 1) / bin) : (uint32_t)(((1ull << 32) + bin - 1) / bin);
+  return p;
+}
+
+template <bool D24>
+__device__ __forceinline__ uint32_t pix_row(uint32_t k, const PixDiv& p) {
+  if constexpr (D24) return (uint32_t)(((uint64_t)((k << p.sh) & 0xffffffu) * (p.m & 0xffffffu)) >> 32);
+  else return magic_div(k, p.mg);
+}
+// k - row W
+template <bool D24>
+__device__ __forceinline__ uint32_t pix_col(uint32_t k, uint32_t row, const PixDiv& p) {
+  if constexpr (D24) return k - (uint32_t)__umul24(row, p.mg.d);
+  else return k - row * p.mg.d;
+}
+// x div bin
+template <bool D24>
+__device__ __forceinline__ uint32_t pix_bin(uint32_t x, const PixDiv& p) {
+  if (!p.mbin) return x;
+  if constexpr (D24) return (uint32_t)(((uint64_t)((x << 8) & 0xffffffu) * (p.mbin & 0xffffffu)) >> 32);
+  else return __umulhi(x, p.mbin);
+}
+
 // Centre of bin index j along an axis, relative to the zero-frequency pixel c, in unbinned
 // pixels: b*j + (b-1)/2 - c.  Exact in double (multiples of 1/2 far below 2^53).
 __host__ __device__ __forceinline__ double bin_centre(int b, int j, int c) {
