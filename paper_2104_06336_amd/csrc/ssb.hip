@@ -49,6 +49,8 @@ struct SsbLayout {
   int ncs;      // column sets (colset_width(Ny) half-spectrum columns each)
   bool fast;    // both scan lengths taken by the fused kernels (powers of two in [32, 1024])
   int64_t nwy;  // waves of the fused column sum (and, for the fast lengths, of the fused adjoint)
+  int wgroups;  // planes of partials of the fused sum with workgroup sums (k_yreduce), 0: not used
+  int64_t nww;  // and its waves
   int64_t nwp;  // waves of a fit's sum over the full columns of G (other scan lengths)
   int64_t nws;  // pieces the refocus sum over the stored values aims at
   int64_t nwq;  // STEM_G_STORE: waves (at most) of the refocus sum over the stored values
@@ -157,6 +159,11 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
   if (g > smallest) g = smallest;
   L->groups = g < 1 ? 1 : g;
   L->nwy = L->fast ? (int64_t)((L->ncs + 3) / 4) * 4 * L->groups : gsum_waves(scan.ny, scan.nx, L->groups);
+  // workgroup sums where the waves' own partials would be more than eight planes
+  // (fewer workgroups, a whole number of rounds of the 512 the GPU holds, were no faster: aberrated sum at
+  // 512 x 512 131 us with 3 planes, 117 us with 5)
+  L->wgroups = L->fast && L->groups > 8 ? (L->groups + 3) / 4 : 0;
+  L->nww = (int64_t)L->ncs * 4 * L->wgroups;
   // the kernels over the stored values: a wave (refocus) or workgroup (adjoint) per column of the
   // whole plane and pixel group, about kPrunedBlocks of them, at most the fused kernels' partial
   // sums
@@ -176,6 +183,7 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
     L->nwq = L->store ? ((nws > scan.nx ? nws : scan.nx) + w - 1) / w * w : 0;
   }
   int64_t nw = L->nwy > L->nwq ? L->nwy : L->nwq;
+  nw = nw > L->nww ? nw : L->nww;
   nw = nw > L->nwp ? nw : L->nwp;
   nw = nw > L->nwa ? nw : L->nwa;
   const int rows = L->ncs > scan.nx ? L->ncs : scan.nx;
@@ -831,6 +839,11 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
   }
   if (ssb->normalize && !refocus && (st = run_pair_count(L, b, ny, nx, s))) return st;
   YArgs a = yargs(L, b, nx);
+  const bool wg = L.wgroups > 0 && !fit;
+  if (wg) {
+    a.wgsum = 1;
+    a.ngroups = L.wgroups;
+  }
   if (refocus) need_finalize(a, L, b, d_status);
   if (L.store && refocus) {
     // Eq. 3 again from the stored double-overlap values
@@ -899,7 +912,7 @@ static int reconstruct(const int32_t* d_idx, const int64_t* d_off, int64_t frame
       if ((st = launch_yreduce(ssb->precision, ny, a, o, chi0, 0, s))) return st;
     }
   }
-  return run_phase(L, b, *scan, L.groups, L.nwy, L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase,
+  return run_phase(L, b, *scan, a.ngroups, wg ? L.nww : L.nwy, L.nchunks, ssb->normalize ? b.npq : nullptr, d_phase,
                    d_T, s, !refocus, fit);
 }
 

@@ -251,6 +251,7 @@ struct YArgs {
   int k0, k1;               // pixels of this launch
   int ngroups;              // pixel groups of [k0, k1)
   int accumulate;           // add to part / wcnt / pdc (a later chunk of pixels)
+  int wgsum;                // fused sum: a workgroup's four waves share a column set (k_yreduce)
   const float2* pg;         // pruned G read (refocus, adjoint)
   float2* pgw;              // PWRITE: pruned G written
   const int64_t* poff;      // pruned offsets [Nx][n_k]
@@ -350,28 +351,84 @@ struct MaskScan {
     }
     return kd_b;
   }
+  // the active pixel after `skip` others at or above from
+  __device__ __forceinline__ int nth(int from, int skip) {
+    for (int kd = from; kd < kd_b;) {
+      const int w = kd >> 6;
+      if (w != mw) {
+        mw = w;
+        mword = mrow[w];
+      }
+      uint64_t bits = mword >> (kd & 63) << (kd & 63);
+      const int n = __builtin_popcountll(bits);
+      if (n > skip) {
+        for (; skip > 0; --skip) bits &= bits - 1;
+        kd = (w << 6) + __builtin_ctzll(bits);
+        return kd < kd_b ? kd : kd_b;
+      }
+      skip -= n;
+      kd = (w + 1) << 6;
+    }
+    return kd_b;
+  }
 };
+
+// The matrix-core outputs v, moved through the wave's LDS buffer into the FFT's register layout.  There the
+// lanes of a register hold neighbouring frequencies (m = lane + 64 j from N = 512 up), so that the wave skips
+// the phase factors of most registers outside a double-overlap set; in the matrix-core layout every register
+// spans all of m and hardly any is skipped.  Measured at a 512 x 512 scan, aberrated, 314 pixels, BF16 (one
+// MI355X): fused sum 134 us instead of 184 us.
+template <typename XF>
+__device__ __forceinline__ void relay_layout(float2* v, float2* buf, int lane) {
+  constexpr int N = XF::N;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    int b, m;
+    XF::out(lane, i, b, m);
+    buf[XF::pad(b * N + m)] = v[i];
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    int b, m;
+    XfFft<N>::out(lane, i, b, m);
+    v[i] = buf[XF::pad(b * N + m)];
+  }
+  wave_lds_sync();
+}
 
 // CHI0: the aberration function and theta are identically zero, so every phase factor of Eq. 3
 // is exactly 1 and the sum adds G itself (conj G for mirrored frequencies): the same values the
 // general path produces for chi = 0, without evaluating them.
-
+//
+// Work split: a wave takes a column set and one of ngroups groups of the pixels, and writes its partial T into
+// plane g of part.  Either a workgroup's waves take four column sets and one group, or (a.wgsum) four groups
+// of one column set (every ng-th active pixel each, so that they end together), whose partials they add
+// in LDS, in order: a quarter of the planes.  The second where the first would make many (a short Ny has few
+// column sets): at a 512 x 512 scan, aberrated, in five chunks of 63 pixels, 19 planes read and written by
+// every chunk took 56 us a launch (FP32; 65 us BF16) against 36 us (46 us) with 5 (one MI355X); with the
+// values written, 176 pixels, 127 against 95 us.  A fit keeps the first, whose sums its gradients carry
+// bit for bit.
 template <typename XF, bool CHI0, bool PWRITE>
 __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
   if (state_unready(a)) return;
   constexpr int NY = XF::N;
+  // with phase factors the matrix-core outputs change to the FFT's register layout (relay_layout)
+  constexpr bool kRelay = XF::kMfma && NY >= 64 && !CHI0;
+  using SL = std::conditional_t<kRelay, XfFft<NY>, XF>;
   __shared__ float2 s_tw[1024];
-  __shared__ float2 s_buf[XF::kMfma ? 1 : 4 * kXWaveStride];
+  __shared__ float2 s_buf[4 * kXWaveStride];
   __shared__ uint4 s_tab[XF::kMfma ? kMfmaTab : 1];
   constexpr int B = 1024 / NY;
-  using SL = XF;
   constexpr int kSlotStride = 16 / SL::kSlots;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nx = a.nx;
   const int nc = nx / 2 + 1;
   const int ncs = (nc + B - 1) / B;                       // column sets
-  const int g = blockIdx.x % a.ngroups;
-  const int cs = (blockIdx.x / a.ngroups) * 4 + wave;     // this wave's column set
+  const int ng = a.wgsum ? 4 * a.ngroups : a.ngroups;     // groups of pixels
+  const int plane = blockIdx.x % a.ngroups;
+  const int g = a.wgsum ? 4 * plane + wave : plane;
+  const int cs = a.wgsum ? blockIdx.x / a.ngroups : (blockIdx.x / a.ngroups) * 4 + wave;  // this wave's column set
   const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
   const PixSrc src = pix_src(a);
   fill_twiddles(s_tw, threadIdx.x, kYThreads);
@@ -384,8 +441,10 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
   }
   float2* buf = s_buf + wave * kXWaveStride;
   const int c0 = cs * B;
-  const int kd_a = a.k0 + (int)((int64_t)(a.k1 - a.k0) * g / a.ngroups);
-  const int kd_b = a.k0 + (int)((int64_t)(a.k1 - a.k0) * (g + 1) / a.ngroups);
+  // the group: a range of the pixels, or (workgroup sums) every ng-th active one
+  const int kd_a = a.wgsum ? a.k0 : a.k0 + (int)((int64_t)(a.k1 - a.k0) * g / ng);
+  const int kd_b = a.wgsum ? a.k1 : a.k0 + (int)((int64_t)(a.k1 - a.k0) * (g + 1) / ng);
+    const int stride = a.wgsum ? ng - 1 : 0;  // active pixels between two of the group's
   float2 accd[16], accm[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) accd[i] = accm[i] = make_float2(0.f, 0.f);
@@ -397,8 +456,8 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
   // a 512 x 512 scan with 314 pixels)
   constexpr int kAhead =
       (CHI0 && !PWRITE && ((!XF::kMfma && XF::kUniformCol && NY != 512) || (XF::kMfma && NY == 1024))) ? 2 : 1;
-  int kd = ms.next(kd_a);
-  int kd1 = kAhead == 2 && kd < kd_b ? ms.next(kd + 1) : kd_b;
+  int kd = ms.nth(kd_a, a.wgsum ? g : 0);
+  int kd1 = kAhead == 2 && kd < kd_b ? ms.nth(kd + 1, stride) : kd_b;
   float2 v[16], v1[kAhead == 2 ? 16 : 1];
   if (kd < kd_b) nld += load_pixel<XF>(src, kd, c0, lane, v);
   if constexpr (kAhead == 2) {
@@ -409,10 +468,10 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
     float2 vn[16];
     if constexpr (kAhead == 2) {
       kdn = kd1;
-      kd1 = kd1 < kd_b ? ms.next(kd1 + 1) : kd_b;
+      kd1 = kd1 < kd_b ? ms.nth(kd1 + 1, stride) : kd_b;
       if (kd1 < kd_b) nld += load_pixel<XF>(src, kd1, c0, lane, vn);
     } else {
-      kdn = ms.next(kd + 1);
+      kdn = ms.nth(kd + 1, stride);
       if (kdn < kd_b) nld += load_pixel<XF>(src, kdn, c0, lane, vn);
     }
     const double2 k = a.kc[kd];
@@ -421,19 +480,20 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
 #pragma unroll
     for (int sl = 0; sl < SL::kSlots; ++sl) {
       int b0, m0;
-      XF::out(lane, sl * kSlotStride, b0, m0);
+      SL::out(lane, sl * kSlotStride, b0, m0);
       const int c = c0 + b0;
       sd[sl] = ColSet{1, 0, 1, 0};
       sm[sl] = ColSet{1, 0, 1, 0};
       if (c < nc) load_colsets(a.cst, (int64_t)kd * nc + c, sd[sl], sm[sl]);
     }
     XF::template run<false>(v, buf, s_tw, s_tab, lane);
+    if constexpr (kRelay) relay_layout<XF>(v, buf, lane);
     if constexpr (PWRITE) {
       // the double-overlap values of this pixel into the pruned array
 #pragma unroll
       for (int sl = 0; sl < SL::kSlots; ++sl) {
         int b0, m0;
-        XF::out(lane, sl * kSlotStride, b0, m0);
+        SL::out(lane, sl * kSlotStride, b0, m0);
         const int c = c0 + b0;
         int64_t pd = 0, pm = 0;
         if (c < nc) {
@@ -444,7 +504,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
         for (int i = 0; i < 16; ++i) {
           if (SL::slot_of(i) != sl) continue;
           int b, m;
-          XF::out(lane, i, b, m);
+          SL::out(lane, i, b, m);
           const int iy = signed_index(m, NY), jy = signed_index((NY - m) & (NY - 1), NY);
           if (c < nc && sd[sl].has(iy)) {
             const int64_t e = pd + set_rank(sd[sl], iy);
@@ -532,7 +592,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
       for (int i = 0; i < 16; ++i) {
         const int sl = SL::slot_of(i);
         int b, m;
-        XF::out(lane, i, b, m);
+        SL::out(lane, i, b, m);
         asm volatile("" : "+v"(m));
         if (sd[sl].has(signed_index(m, NY))) {
           accd[i].x += v[i].x;
@@ -551,7 +611,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
 #pragma unroll
         for (int sl = 0; sl < SL::kSlots; ++sl) {
           int b0, m0;
-          XF::out(lane, sl * kSlotStride, b0, m0);
+          SL::out(lane, sl * kSlotStride, b0, m0);
           // one column polynomial live at a time: the slot's direct frequencies, then its mirrored
           // ones, each polynomial formed only after the previous pass (formed all at once they stay
           // live together and spill at N = 512, two slots per lane)
@@ -563,7 +623,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
             for (int i = 0; i < 16; ++i) {
               if (SL::slot_of(i) != sl) continue;
               int b, m;
-              XF::out(lane, i, b, m);
+              SL::out(lane, i, b, m);
               // keep the per-register frequency arithmetic inside the pixel loop: hoisted out of it,
               // the 16 registers' frequencies stay live across the loop and cost occupancy
               asm volatile("" : "+v"(m));
@@ -585,7 +645,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
             for (int i = 0; i < 16; ++i) {
               if (SL::slot_of(i) != sl) continue;
               int b, m;
-              XF::out(lane, i, b, m);
+              SL::out(lane, i, b, m);
               asm volatile("" : "+v"(m));
               const int jy = signed_index((NY - m) & (NY - 1), NY);
               if (sm[sl].has(jy)) {
@@ -603,7 +663,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
 #pragma unroll
         for (int sl = 0; sl < SL::kSlots; ++sl) {
           int b0, m0;
-          XF::out(lane, sl * kSlotStride, b0, m0);
+          SL::out(lane, sl * kSlotStride, b0, m0);
           const int c = c0 + b0;
           const ChiCol chd = chi_column(o.lk * (k.x - (double)signed_index(c, nx) * o.sx), o);
           const ChiCol chm = chi_column(o.lk * (k.x - (double)signed_index(nx - c, nx) * o.sx), o);
@@ -611,7 +671,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
           for (int i = 0; i < 16; ++i) {
             if (SL::slot_of(i) != sl) continue;
             int b, m;
-            XF::out(lane, i, b, m);
+            SL::out(lane, i, b, m);
             // keep the per-register frequency arithmetic inside the pixel loop: hoisted out of it, the
             // 16 registers' frequencies stay live across the loop and cost occupancy
             asm volatile("" : "+v"(m));
@@ -647,23 +707,50 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
       for (int i = 0; i < 16; ++i) v[i] = vn[i];
     }
   }
-  float2* pgp = a.part + (int64_t)g * nx * NY;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  float2* pgp = a.part + (int64_t)plane * nx * NY;
+  auto put = [&](int i, float2 vd, float2 vm) {
     int b, m;
-    XF::out(lane, i, b, m);
+    SL::out(lane, i, b, m);
     const int c = c0 + b;
-    if (c >= nc) continue;
+    if (c >= nc) return;
     float2* pd = pgp + (int64_t)c * NY + m;
     float2* pm = pgp + (int64_t)(nx - c) * NY + ((NY - m) & (NY - 1));
     const bool mir = c > 0 && 2 * c < nx;
     if (a.accumulate) {
-      *pd = cadd(*pd, accd[i]);
-      if (mir) *pm = cadd(*pm, accm[i]);
+      *pd = cadd(*pd, vd);
+      if (mir) *pm = cadd(*pm, vm);
     } else {
-      *pd = accd[i];
-      if (mir) *pm = accm[i];
+      *pd = vd;
+      if (mir) *pm = vm;
     }
+  };
+  if (a.wgsum) {
+    // the four waves' sums through LDS: wave w adds registers 4w .. 4w + 3 of each lane
+    float2 td[4], tm[4];
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s_buf[wave * 1024 + i * 64 + lane] = side ? accm[i] : accd[i];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float2* p = s_buf + (4 * wave + q) * 64 + lane;
+        const float2 x = cadd(cadd(cadd(p[0], p[1024]), p[2048]), p[3072]);
+        if (side) tm[q] = x;
+        else td[q] = x;
+      }
+    }
+    // the registers of this wave's quarter, at compile-time positions for the index map
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (wave == w) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) put(4 * w + q, td[q], tm[q]);
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) put(i, accd[i], accm[i]);
   }
   unsigned long long cc = (unsigned long long)cnt + ((unsigned long long)nld << kLoadShift);
   for (int off = 32; off > 0; off >>= 1) cc += __shfl_xor(cc, off);
@@ -888,18 +975,18 @@ int launch_xstage_p(int nx, const DT* D, int ny, int ry0, int nr, int64_t nrows,
   return STEM_OK;
 }
 
-// grid of the fused column kernels: column sets in fours (one per wave) times pixel groups
-inline dim3 ygrid(int ny, int nx, int ngroups) {
+// grid of the fused column kernels: column sets in fours (one per wave), or one by one, times the planes
+inline dim3 ygrid(int ny, int nx, int ngroups, int wgsum) {
   const int B = 1024 / ny;
   const int ncs = (nx / 2 + 1 + B - 1) / B;
-  return dim3((unsigned)(((ncs + 3) / 4) * ngroups));
+  return dim3((unsigned)((wgsum ? ncs : (ncs + 3) / 4) * ngroups));
 }
 
 // the fused sum over pixels [a.k0, a.k1) with the transform policy of precision PREC; pwrite: also
 // write the pruned G
 template <int PREC>
 int launch_yreduce_p(int ny, const YArgs& a, const Optics& o, int chi0, int pwrite, hipStream_t s) {
-  const dim3 grid = ygrid(ny, a.nx, a.ngroups), blk(kYThreads);
+  const dim3 grid = ygrid(ny, a.nx, a.ngroups, a.wgsum), blk(kYThreads);
   STEM_TRACE(PREC == STEM_FFT_FP32 ? "ssb_yreduce" : "ssb_yreduce_mfma", s);
   const int st = with_n(ny, [&](auto nc) {
     using XF = typename XfSel<decltype(nc)::value, PREC>::type;
@@ -919,7 +1006,7 @@ int launch_yreduce_p(int ny, const YArgs& a, const Optics& o, int chi0, int pwri
 
 template <int PREC>
 int launch_yadjoint_p(int ny, const YArgs& a, const Optics& o, hipStream_t s) {
-  const dim3 grid = ygrid(ny, a.nx, a.ngroups), blk(kYThreads);
+  const dim3 grid = ygrid(ny, a.nx, a.ngroups, 0), blk(kYThreads);
   STEM_TRACE(PREC == STEM_FFT_FP32 ? "ssb_yadjoint" : "ssb_yadjoint_mfma", s);
   const int st = with_n(ny, [&](auto nc) {
     using XF = typename XfSel<decltype(nc)::value, PREC>::type;
