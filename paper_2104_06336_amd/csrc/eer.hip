@@ -18,7 +18,8 @@
 
 namespace stem {
 
-constexpr int kComThreads = 256;   // = kComFrames: thread t finishes frame t
+constexpr int kComThreads = 256;
+constexpr int kComFrames = 256;  // of the run-length re-coding: thread t takes frame t
 
 // ---------------------------------------------------------------------------------------------
 // validation
@@ -88,15 +89,17 @@ __device__ __forceinline__ bool load_rel_offsets(const int64_t* __restrict__ off
 }
 
 // ---------------------------------------------------------------------------------------------
-// Staging of a workgroup's events in LDS: the events [a0, a0 + n) (absolute indices, n <= kComWin)
+// Staging of a workgroup's events in LDS: the events [a0, a0 + n) (absolute indices, n <= WIN)
 // are copied as whole 16-byte lines from the aligned position at or below a0; s[sh + j] then holds
 // event a0 + j (sh < 4 is returned).  Every line holds at least one of the events, so it lies in
 // the event array's pages; its other entries land outside [sh, sh + n) and are never read.  Each
 // thread issues kStageGroups loads before its LDS stores: a window takes one round.
-constexpr int kComWin = 12288;
-constexpr int kStageGroups = kComWin / (4 * kComThreads);
+constexpr int kComWin = 12288;  // the run-length re-coding's window
+constexpr int kSumWin = 6144;   // and that of the per-frame sums
 
+template <int WIN>
 __device__ __forceinline__ int stage_events(const int32_t* __restrict__ idx, int64_t a0, int n, int32_t* s) {
+  constexpr int kStageGroups = WIN / (4 * kComThreads);
   const int sh = (int)((((uintptr_t)(idx + a0)) & 15) >> 2);
   const int32_t* ib = idx + (a0 - sh);
   const int ng = (n + sh + 3) >> 2;
@@ -117,13 +120,44 @@ __device__ __forceinline__ int stage_events(const int32_t* __restrict__ idx, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// centre of mass: a workgroup owns kComFrames consecutive frames.  Their events are staged in
-// LDS in windows of kComWin (coalesced 16-byte loads); thread t then sums the events of frame t
-// from LDS with four independent accumulators (int32 within a window, int64 across windows).
+// Per-frame sums (centre of mass, annuli): a workgroup owns kComThreads / FT consecutive frames, whose events
+// are staged in LDS in windows of kSumWin (coalesced 16-byte loads); the FT threads of a frame take its
+// events in turn and add their sums by lane exchange.  With one thread per frame, 256 frames and windows of
+// 12288 events a workgroup, a 256 x 256 scan made one workgroup per compute unit and three windows each, and a
+// wave ran as long as its longest frame.  Centre of mass, one MI355X: 256 x 256 (100 events a frame) 14
+// instead of 29 us, 512 x 512 (60) 15 instead of 25 us, 1024 x 1024 (40) 42 instead of 46 us (4.6 TB/s, about
+// the rate of a copy); two annuli at 1024 x 1024 41 instead of 51 us.
+//
+// FT is 4, and 2 from 2^19 frames on, where there are workgroups enough (1024 x 1024: 50 us with 4).
+inline int frame_threads(int64_t n_frames) { return n_frames < (1 << 19) ? 4 : 2; }
 
-constexpr int kComFrames = 256;
+// The frames' offsets into s_off; false (reported) when the block holds 2^30 events or more, which the 32-bit
+// relative positions cannot address.
+__device__ __forceinline__ bool load_offsets(const int64_t* __restrict__ off, int64_t fb, int nf, int64_t* s_off,
+                                             int32_t* status) {
+  if ((int)threadIdx.x <= nf) s_off[threadIdx.x] = off[fb + threadIdx.x];
+  __syncthreads();
+  if (s_off[nf] - s_off[0] < (1ll << 30)) return true;
+  if (threadIdx.x == 0) report(status, STEM_EOVERFLOW);
+  return false;
+}
 
-template <bool D24>
+// f(k) for the events of the thread's frame in the window's LDS positions [lo, hi): every FT-th from the
+// thread's own, four read ahead
+template <int FT, typename F>
+__device__ __forceinline__ void frame_events(const int32_t* s_ev, int lo, int hi, int part, F&& f) {
+  int e = lo + part;
+  for (; e + 3 * FT < hi; e += 4 * FT) {
+    int32_t k[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k[j] = s_ev[e + j * FT];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f(k[j]);
+  }
+  for (; e < hi; e += FT) f(s_ev[e]);
+}
+
+template <bool D24, int FT>
 __global__ void __launch_bounds__(kComThreads) k_com(const int32_t* __restrict__ idx,
                                                      const int64_t* __restrict__ off,
                                                      int64_t frame0, int64_t n_frames, PixDiv div,
@@ -132,55 +166,54 @@ __global__ void __launch_bounds__(kComThreads) k_com(const int32_t* __restrict__
                                                      float* __restrict__ com32,
                                                      int32_t* __restrict__ counts,
                                                      int32_t* status) {
-  __shared__ __align__(16) int32_t s_ev[kComWin + 8];
-  __shared__ int32_t s_rel[kComFrames + 1];
-  __shared__ int64_t s_base;
-  const int t = threadIdx.x;
-  const int64_t fb = frame0 + (int64_t)blockIdx.x * kComFrames;
+  constexpr int kSumFrames = kComThreads / FT;
+  __shared__ __align__(16) int32_t s_ev[kSumWin + 8];
+  __shared__ int64_t s_off[kSumFrames + 1];
+  const int f = threadIdx.x / FT, part = threadIdx.x % FT;
+  const int64_t fb = frame0 + (int64_t)blockIdx.x * kSumFrames;
   const int64_t left = frame0 + n_frames - fb;
-  const int nf = (int)(left < kComFrames ? left : kComFrames);
-  if (!load_rel_offsets(off, fb, nf, s_rel, &s_base, status)) return;
-  __syncthreads();
-  const int span = s_rel[nf];
-  const int lo_t = t < nf ? s_rel[t] : 0, hi_t = t < nf ? s_rel[t + 1] : 0;
+  const int nf = (int)(left < kSumFrames ? left : kSumFrames);
+  if (!load_offsets(off, fb, nf, s_off, status)) return;
+  const int64_t base = s_off[0];
+  const int span = (int)(s_off[nf] - base);
+  const int lo_f = f < nf ? (int)(s_off[f] - base) : 0, hi_f = f < nf ? (int)(s_off[f + 1] - base) : 0;
   int64_t sx = 0, sy = 0;
   int32_t bad = 0;
-  for (int w0 = 0; w0 < span; w0 += kComWin) {
-    const int wn = span - w0 < kComWin ? span - w0 : kComWin;
+  for (int w0 = 0; w0 < span; w0 += kSumWin) {
+    const int wn = span - w0 < kSumWin ? span - w0 : kSumWin;
+    if (w0 > 0) __syncthreads();
+    const int sh = stage_events<kSumWin>(idx, base + w0, wn, s_ev);
     __syncthreads();
-    const int sh = stage_events(idx, s_base + w0, wn, s_ev);
-    __syncthreads();
-    const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
-    const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
+    const int lo = (lo_f > w0 ? lo_f : w0) - w0 + sh;
+    const int hi = (hi_f < w0 + wn ? hi_f : w0 + wn) - w0 + sh;
     // out-of-range indices are counted (and reported) and contribute nothing; no branches.  With the rows
     // ky of the indices k, the columns' sum is the sum of k less W times the sum of ky, here modulo
-    // 2^32: a window's columns and rows sum to less (kComWin W, kComWin H < 2^32 for sides below 2^18;
+    // 2^32: a window's columns and rows sum to less (kSumWin W, kSumWin H < 2^32 for sides below 2^18;
     // larger ones sum in 64 bits).
     using S = std::conditional_t<D24, uint32_t, uint64_t>;
-    S sk[4] = {0, 0, 0, 0}, sr[4] = {0, 0, 0, 0};
-    uint32_t nin = 0;
-    auto add = [&](int j, int32_t k) {
+    S tk = 0, tr = 0;
+    uint32_t nin = 0, n = 0;
+    frame_events<FT>(s_ev, lo, hi, part, [&](int32_t k) {
       const bool in = (uint32_t)k < (uint32_t)npix;
+      ++n;
       nin += in ? 1u : 0u;
       const uint32_t kk = in ? (uint32_t)k : 0u;
-      sk[j] += kk;
-      sr[j] += pix_row<D24>(kk, div);
-    };
-    int e = lo;
-    for (; e + 4 <= hi; e += 4) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) add(j, s_ev[e + j]);
-    }
-    for (; e < hi; ++e) add(0, s_ev[e]);
-    if (lo < hi && nin != (uint32_t)(hi - lo)) bad = STEM_ERANGE;
-    const S tk = (sk[0] + sk[1]) + (sk[2] + sk[3]), tr = (sr[0] + sr[1]) + (sr[2] + sr[3]);
+      tk += kk;
+      tr += pix_row<D24>(kk, div);
+    });
+    if (nin != n) bad = STEM_ERANGE;
     const S tc = tk - tr * (S)div.mg.d;
     sx += (int64_t)tc - (int64_t)cx * nin;
     sy += (int64_t)tr - (int64_t)cy * nin;
   }
-  if (t < nf) {
-    const int64_t fr = fb + t;
-    const int64_t n = hi_t - lo_t;
+#pragma unroll
+  for (int o = 1; o < FT; o <<= 1) {
+    sx += __shfl_xor(sx, o);
+    sy += __shfl_xor(sy, o);
+  }
+  if (f < nf && part == 0) {
+    const int64_t fr = fb + f;
+    const int64_t n = hi_f - lo_f;
     const double x = n > 0 ? (double)sx / (double)n : 0.0;
     const double y = n > 0 ? (double)sy / (double)n : 0.0;
     if (com64) {
@@ -200,10 +233,11 @@ int launch_com(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
                const stem_det& det, int64_t nplane, double* com64, float* com32, int32_t* counts,
                int32_t* status, hipStream_t stream) {
   if (n_frames == 0) return STEM_OK;
-  const int64_t blocks = (n_frames + kComFrames - 1) / kComFrames;
+  const int ft = frame_threads(n_frames);
+  const int64_t blocks = (n_frames + kComThreads / ft - 1) / (kComThreads / ft);
   STEM_TRACE("com_moments", stream);
   const PixDiv div = make_pixdiv(det.W, det.H, 1);
-  const auto fn = div.d24 ? k_com<true> : k_com<false>;
+  const auto fn = ft == 4 ? (div.d24 ? k_com<true, 4> : k_com<false, 4>) : (div.d24 ? k_com<true, 2> : k_com<false, 2>);
   hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kComThreads), 0, stream, idx, off, frame0, n_frames, div,
                      det.cx, det.cy, det.W * det.H, nplane, com64, com32, counts, status);
   STEM_LAUNCH_CHECK();
@@ -211,9 +245,8 @@ int launch_com(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
 }
 
 // ---------------------------------------------------------------------------------------------
-// virtual annular detectors: the same staging as k_com; thread t counts the events of frame t in
-// each annulus [lo_j, hi_j) of squared pixel distance (exact int64 thresholds)
-
+// virtual annular detectors: the same split as k_com; a frame's threads count its events in each annulus
+// [lo_j, hi_j) of squared pixel distance (exact int64 thresholds)
 //
 // D24 (sides below 2^15 and the zero-frequency pixel on the detector, so d^2 < 2^32): the squared distance by
 // 24-bit multiplications and one unsigned comparison per annulus.
@@ -223,35 +256,35 @@ struct Annuli {
   uint32_t lo32[STEM_MAX_ANNULI], len32[STEM_MAX_ANNULI];  // lo and hi - lo, cut at 2^32 - 1
 };
 
-template <int NA, bool D24>
+template <int NA, bool D24, int FT>
 __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restrict__ idx,
                                                          const int64_t* __restrict__ off, int64_t frame0,
                                                          int64_t n_frames, PixDiv div, int32_t cx, int32_t cy,
-                                                         int32_t npix, Annuli an, int64_t F,
+                                                         int32_t npix, int32_t n_det, Annuli an, int64_t F,
                                                          int32_t* __restrict__ out, int32_t* status) {
-  __shared__ __align__(16) int32_t s_ev[kComWin + 8];
-  __shared__ int32_t s_rel[kComFrames + 1];
-  __shared__ int64_t s_base;
-  const int t = threadIdx.x;
-  const int64_t fb = frame0 + (int64_t)blockIdx.x * kComFrames;
+  constexpr int kSumFrames = kComThreads / FT;
+  __shared__ __align__(16) int32_t s_ev[kSumWin + 8];
+  __shared__ int64_t s_off[kSumFrames + 1];
+  const int f = threadIdx.x / FT, part = threadIdx.x % FT;
+  const int64_t fb = frame0 + (int64_t)blockIdx.x * kSumFrames;
   const int64_t left = frame0 + n_frames - fb;
-  const int nf = (int)(left < kComFrames ? left : kComFrames);
-  if (!load_rel_offsets(off, fb, nf, s_rel, &s_base, status)) return;
-  __syncthreads();
-  const int span = s_rel[nf];
-  const int lo_t = t < nf ? s_rel[t] : 0, hi_t = t < nf ? s_rel[t + 1] : 0;
+  const int nf = (int)(left < kSumFrames ? left : kSumFrames);
+  if (!load_offsets(off, fb, nf, s_off, status)) return;
+  const int64_t base = s_off[0];
+  const int span = (int)(s_off[nf] - base);
+  const int lo_f = f < nf ? (int)(s_off[f] - base) : 0, hi_f = f < nf ? (int)(s_off[f + 1] - base) : 0;
   int32_t cnt[NA];
 #pragma unroll
   for (int j = 0; j < NA; ++j) cnt[j] = 0;
   uint32_t nbad = 0;
-  for (int w0 = 0; w0 < span; w0 += kComWin) {
-    const int wn = span - w0 < kComWin ? span - w0 : kComWin;
+  for (int w0 = 0; w0 < span; w0 += kSumWin) {
+    const int wn = span - w0 < kSumWin ? span - w0 : kSumWin;
+    if (w0 > 0) __syncthreads();
+    const int sh = stage_events<kSumWin>(idx, base + w0, wn, s_ev);
     __syncthreads();
-    const int sh = stage_events(idx, s_base + w0, wn, s_ev);
-    __syncthreads();
-    const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
-    const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
-    auto add = [&](int32_t k) {
+    const int lo = (lo_f > w0 ? lo_f : w0) - w0 + sh;
+    const int hi = (hi_f < w0 + wn ? hi_f : w0 + wn) - w0 + sh;
+    frame_events<FT>(s_ev, lo, hi, part, [&](int32_t k) {
       const bool in = (uint32_t)k < (uint32_t)npix;
       nbad += in ? 0u : 1u;
       const uint32_t kk = in ? (uint32_t)k : 0u;
@@ -267,20 +300,13 @@ __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restri
 #pragma unroll
         for (int j = 0; j < NA; ++j) cnt[j] += (in && d2 >= an.lo[j] && d2 < an.hi[j]) ? 1 : 0;
       }
-    };
-    int e = lo;
-    for (; e + 4 <= hi; e += 4) {
-      int32_t k[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) k[j] = s_ev[e + j];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) add(k[j]);
-    }
-    for (; e < hi; ++e) add(s_ev[e]);
+    });
   }
-  if (t < nf) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j) out[(int64_t)j * F + fb + t] = cnt[j];
+  for (int j = 0; j < NA; ++j) {
+#pragma unroll
+    for (int o = 1; o < FT; o <<= 1) cnt[j] += __shfl_xor(cnt[j], o);
+    if (f < nf && part == 0 && j < n_det) out[(int64_t)j * F + fb + f] = cnt[j];  // NA is n_det rounded up
   }
   if (nbad) report(status, STEM_ERANGE);
 }
@@ -419,7 +445,7 @@ __global__ void __launch_bounds__(kComThreads) k_decode_rle(const int32_t* __res
   for (int w0 = 0; w0 < span; w0 += kComWin) {
     const int wn = span - w0 < kComWin ? span - w0 : kComWin;
     __syncthreads();
-    const int sh = stage_events(dist, s_base + w0, wn, s_ev);
+    const int sh = stage_events<kComWin>(dist, s_base + w0, wn, s_ev);
     __syncthreads();
     const int lo = (lo_t > w0 ? lo_t : w0) - w0 + sh;
     const int hi = (hi_t < w0 + wn ? hi_t : w0 + wn) - w0 + sh;
@@ -1114,7 +1140,8 @@ extern "C" int virtual_annular(const int32_t* d_idx, const int64_t* d_off, int64
   }
   if (n_frames == 0) return STEM_OK;
   hipStream_t s = (hipStream_t)stream_;
-  const int64_t blocks = (n_frames + kComFrames - 1) / kComFrames;
+  const int ft = frame_threads(n_frames);
+  const int64_t blocks = (n_frames + kComThreads / ft - 1) / (kComThreads / ft);
   for (int j = 0; j < STEM_MAX_ANNULI; ++j) {
     const int64_t top = 0xffffffffll, lo = an.lo[j] < top ? an.lo[j] : top, hi = an.hi[j] < top ? an.hi[j] : top;
     an.lo32[j] = (uint32_t)lo;
@@ -1127,9 +1154,10 @@ extern "C" int virtual_annular(const int32_t* d_idx, const int64_t* d_off, int64
   const int npix = det->W * det->H;
   auto go = [&](auto na) {
     constexpr int NA = decltype(na)::value;
-    const auto fn = d24 ? k_annular<NA, true> : k_annular<NA, false>;
-    hipLaunchKernelGGL(fn, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, div, det->cx, det->cy, npix, an, F, d_out,
-                       d_status);
+    const auto fn = ft == 4 ? (d24 ? k_annular<NA, true, 4> : k_annular<NA, false, 4>)
+                            : (d24 ? k_annular<NA, true, 2> : k_annular<NA, false, 2>);
+    hipLaunchKernelGGL(fn, grid, blk, 0, s, d_idx, d_off, frame0, n_frames, div, det->cx, det->cy, npix, n_det, an, F,
+                       d_out, d_status);
   };
   if (n_det <= 1) go(std::integral_constant<int, 1>{});
   else if (n_det <= 2) go(std::integral_constant<int, 2>{});
