@@ -71,7 +71,7 @@ typedef struct {
 
 /* Scan grid: Ny x Nx probe positions, spacing `step` angstrom.  The transforms take Ny and Nx
  * of the form 2^a 3^b 5^c, even, in [16, 4096] (the fused single-wave kernels serve powers of
- * two in [32, 1024]; the other lengths run a mixed-radix LDS FFT and separate sum kernels);
+ * two in [32, 1024]; the other lengths run a mixed-radix LDS FFT and its fused sum);
  * centre of mass alone takes any size. */
 typedef struct {
   int32_t ny, nx;
