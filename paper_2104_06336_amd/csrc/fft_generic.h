@@ -9,7 +9,7 @@
 // each pass in place.
 //
 // What bounds it is LDS traffic, index arithmetic and barriers, all per pass, so the plan takes the
-// fewest passes it can: radices up to 16 (1000 = 10.10.10, 96 = 6.16, 2000 = 5.5.8.10), the composite
+// fewest passes it can: radices up to 16 (1000 = 10.10.10, 96 = 8.12, 2000 = 5.5.8.10), the composite
 // ones in registers (products of coprime lengths by the prime-factor map, without twiddles).  The
 // twiddles lie in LDS per pass in the order the butterflies read them ([q - 1][j mod Ns], N - R0
 // entries in all), the quotients by m and Ns are multiply-high by constants of the plan.  Against radices
