@@ -239,17 +239,44 @@ struct ColSet {
   __device__ __forceinline__ bool empty() const { return a0 > a1; }
 };
 
-__device__ __forceinline__ ColSet col_set(double kx, double ky, int ix, int ny, const Optics& o) {
-  const double qx = (double)ix * o.sx;
-  ColSet cs;
-  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, -1, ny, cs.a0, cs.a1);
-  if (cs.a0 > cs.a1) {
-    cs.b0 = 1;
-    cs.b1 = 0;
-    return cs;
+// Interval of -iy for the iy in [lo, hi] of one disk along column ix: the other disk's interval along -ix, as
+// K - Q at (-ix, -iy) is K + Q at (ix, iy), in the same rounded operations.  iy = -ny/2 has no negative in
+// range: its membership (first) is tested by the caller, and joins or makes the interval.
+__device__ __forceinline__ void mirror_interval(int lo, int hi, int ny, bool first, int& lo_out, int& hi_out) {
+  int l = -hi, h = -lo < ny / 2 - 1 ? -lo : ny / 2 - 1;
+  if (lo > hi || l > h) {
+    l = 1;
+    h = 0;
   }
-  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, +1, ny, cs.b0, cs.b1);
-  return cs;
+  if (first) {
+    if (l > h) h = -ny / 2;
+    l = -ny / 2;
+  }
+  lo_out = l;
+  hi_out = h;
+}
+
+// The sets along column ix and, with mirror, along -ix: two disk intervals serve both (four took the binning of
+// a 64 x 64 scan, which waits for them, 22 us instead of 15 us).
+__device__ __forceinline__ void col_sets(double kx, double ky, int ix, int ny, const Optics& o, bool mirror, ColSet& d,
+                                         ColSet& m) {
+  const double qx = (double)ix * o.sx;
+  m = ColSet{1, 0, 1, 0};
+  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, -1, ny, d.a0, d.a1);
+  d.b0 = 1;
+  d.b1 = 0;
+  if (!mirror && d.a0 > d.a1) return;
+  int b0, b1;
+  disk_interval(kx, ky, qx, o.sy, o.rsy, o.r2, +1, ny, b0, b1);
+  if (mirror) {
+    const double qf = (double)(-ny / 2) * o.sy;
+    mirror_interval(b0, b1, ny, near_disk(kx, ky, -qx, qf, o.r2, -1), m.a0, m.a1);
+    if (m.a0 <= m.a1) mirror_interval(d.a0, d.a1, ny, near_disk(kx, ky, -qx, qf, o.r2, +1), m.b0, m.b1);
+  }
+  if (d.a0 <= d.a1) {
+    d.b0 = b0;
+    d.b1 = b1;
+  }
 }
 
 // The double-overlap interval table of the fused column sum and its active-pixel mask: for
@@ -280,9 +307,8 @@ __device__ __forceinline__ uint64_t sets_columns(const SetsJob& j, int64_t word,
   if (kd < j.n_k) {
     const int c1 = cs * B + B < nc ? cs * B + B : nc;
     for (int c = cs * B + from; c < c1; c += step) {
-      const ColSet d = col_set(k.x, k.y, signed_index(c, j.nx), j.ny, j.o);
-      ColSet m{1, 0, 1, 0};
-      if (c > 0 && 2 * c < j.nx) m = col_set(k.x, k.y, signed_index(j.nx - c, j.nx), j.ny, j.o);
+      ColSet d, m;
+      col_sets(k.x, k.y, signed_index(c, j.nx), j.ny, j.o, c > 0 && 2 * c < j.nx, d, m);
       j.cst[(int64_t)kd * nc + c] = make_int4(pk(d.a0, d.a1), pk(d.b0, d.b1), pk(m.a0, m.a1), pk(m.b0, m.b1));
       any = any || d.a0 <= d.a1 || m.a0 <= m.a1;
     }
