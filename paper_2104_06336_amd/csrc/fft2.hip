@@ -511,21 +511,27 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
   }
 }
 
+int gen_fft_rows(const GPlan& p, int64_t nrows) {
+  const int most = gen_max_rows(p, kGenThreads, kGenEpt);
+  const int64_t fill = nrows / 256 > 1 ? nrows / 256 : 1;
+  int64_t rb = kGenMax / p.n;
+  rb = rb > most ? most : rb;
+  return (int)(rb > fill ? fill : rb);
+}
+
 static int launch_generic(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream) {
   GPlan p;
   if (!gen_plan(n, p)) return STEM_EINVAL;
-  int64_t rb = kGenMax / n;
-  if (rb > gen_max_rows(p, kGenThreads, kGenEpt)) rb = gen_max_rows(p, kGenThreads, kGenEpt);
-  if (rb > a.nrows / 256) rb = a.nrows / 256;
-  if (rb < 1) rb = 1;
+  const int rb = gen_fft_rows(p, a.nrows);
+  if (rb < 1) return STEM_EINVAL;
   const int64_t batches = (a.nrows + rb - 1) / rb;
-  const size_t lds = gen_lds(p, (int)rb, p.len);
+  const size_t lds = gen_lds(p, rb, p.len);
   auto go = [&](auto mode, auto seg) {
     const auto fn = k_grow_fft<decltype(mode)::value, decltype(seg)::value>;
     const int res = resident_blocks((const void*)fn, kGenThreads, lds);
     const int64_t cap = res > 0 ? res : 1024;
     hipLaunchKernelGGL(fn, dim3((unsigned)(batches < cap ? batches : cap)), dim3(kGenThreads), lds, stream, a, p,
-                       (int)rb, inverse ? 1 : 0, (int)out);
+                       rb, inverse ? 1 : 0, (int)out);
   };
   using T_ = std::true_type;
   using F_ = std::false_type;
@@ -618,22 +624,30 @@ __global__ void __launch_bounds__(kGenXThreads, 4) k_grow_x(const DT* __restrict
   }
 }
 
-int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2* X, hipStream_t stream) {
-  GPlan p;
-  if (!gen_plan(n, p) || (ny & 1) || (nrows & 1) || nrows <= 0 || nrows >= (1ll << 31)) return STEM_EINVAL;
-  STEM_TRACE("xstage_fft", stream);
-  // row pairs per workgroup: 64 KB of rows at most; past 8 (runs of 128 bytes) only while every
-  // compute unit still gets two workgroups
+int gen_x_rows(const GPlan& p, int64_t nrows, int& stride) {
+  // row pairs per workgroup: 64 KB of rows at most where that is more than one pair; past 8 (runs of
+  // 128 bytes) only while every compute unit still gets two workgroups
   const int most = gen_max_rows(p, kGenXThreads, kGenXEpt);
+  if (most < 1) return -1;
   int lrb = 0;
   while ((2 << lrb) <= most && (2 << lrb) * p.len <= 8704 &&
          ((2 << lrb) <= 8 || nrows >= (4ll << lrb) * 512))
     ++lrb;
   // the row stride: 1 / rb of the banks apart modulo the 32 of 8 bytes, so that the rb rows of one
   // frequency, read together by the split, lie in different banks
-  int stride = p.len;
+  stride = p.len;
   const int step = 32 >> lrb ? 32 >> lrb : 1;
   while (lrb && (stride & 31) != step) ++stride;
+  return lrb;
+}
+
+int launch_gen_x(int n, const void* D, int d_bits, int ny, int64_t nrows, float2* X, hipStream_t stream) {
+  GPlan p;
+  if (!gen_plan(n, p) || (ny & 1) || (nrows & 1) || nrows <= 0 || nrows >= (1ll << 31)) return STEM_EINVAL;
+  int stride;
+  const int lrb = gen_x_rows(p, nrows, stride);
+  if (lrb < 0) return STEM_EINVAL;
+  STEM_TRACE("xstage_fft", stream);
   const size_t lds = gen_lds(p, 1 << lrb, stride);
   auto go = [&](auto dt) {
     using DT = decltype(dt);

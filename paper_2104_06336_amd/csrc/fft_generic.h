@@ -68,6 +68,11 @@ inline int gen_max_rows(const GPlan& p, int threads, int ept) {
   return rb;
 }
 
+// Rows a workgroup of the row passes takes of nrows, and the binary logarithm of the row pairs one of the
+// row transform of counts takes, with its LDS row stride (-1: none).
+int gen_fft_rows(const GPlan& p, int64_t nrows);
+int gen_x_rows(const GPlan& p, int64_t nrows, int& stride);
+
 // LDS of a workgroup in float2: the twiddles (an even number of entries, so that what follows is
 // 16-byte aligned), then the rows (at least the 128 double2 that gen_twiddles works in)
 __host__ __device__ inline int gen_tw_size(const GPlan& p) { return (p.ntw + 1) & ~1; }

@@ -1,6 +1,7 @@
 // The column transform fused with Eq. 3 at any scan length (ssb_gen.hip): layout and launcher.
 #pragma once
 
+#include "fft_generic.h"
 #include "ssb_fused.h"
 
 namespace stem {
@@ -24,6 +25,10 @@ inline int gsum_groups(int ny, int nx, int pixels, bool chunked) {
 inline int64_t gsum_waves(int ny, int nx, int ngroups) {
   return (int64_t)(nx / 2 + 1) * ngroups * (gsum_threads(ny) / 64);
 }
+
+// Pixels a workgroup transforms together and the plan of ny: at least one at every length the library
+// transforms, 0 if ny has no plan.
+int gsum_rows(int ny, GPlan& p);
 
 // The sum over the pixels [a.k0, a.k1), whose row-transformed columns are at a.X, in a.ngroups groups;
 // pwrite: also store the double-overlap values as the pruned array.

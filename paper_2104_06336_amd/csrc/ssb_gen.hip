@@ -18,7 +18,6 @@
 // elements it took 505 and 75 us.
 #include "ssb_gen.h"
 
-#include "fft_generic.h"
 #include "trace.h"
 
 namespace stem {
@@ -27,8 +26,8 @@ namespace stem {
 // SIMD), else 16 (two).
 static int gsum_ept(const GPlan& p) { return p.p[p.np - 1].r <= 12 ? 12 : 16; }
 constexpr int kGsBatch = 64;   // pixels whose descriptors are gathered at once
-constexpr int kGsRows = 4352;  // LDS elements of the rows: 34 KB, so that the registers, not LDS, set
-                               // the residency
+constexpr int kGsRows = 4352;  // LDS elements of the rows where more than one fits: 34 KB, so that the
+                               // registers, not LDS, set the residency (one padded row alone may be longer)
 
 // The pixels of a batch with a pair in the column or its mirror: their packed sets, the offsets of
 // their runs of the pruned array and the phase polynomials of both columns.
@@ -237,12 +236,11 @@ __global__ void __launch_bounds__(T, EPT == 12 ? 3 : 2) k_gsum(YArgs a, Optics o
   if (lane == 0) a.wcnt[wid] = a.accumulate ? a.wcnt[wid] + cc : cc;
 }
 
-// pixels transformed together; 0 if ny has no plan
-static int gsum_rows(int ny, GPlan& p) {
+int gsum_rows(int ny, GPlan& p) {
   if (!gen_plan(ny, p)) return 0;
   const int T = gsum_threads(ny);
   int rb = gen_max_rows(p, T, gsum_ept(p));
-  const int one = T / p.p[p.np - 1].m, lds = kGsRows / p.len;
+  const int one = T / p.p[p.np - 1].m, lds = kGsRows / p.len > 1 ? kGsRows / p.len : 1;
   rb = one < rb ? one : rb;
   rb = lds < rb ? lds : rb;
   return rb < kGsBatch ? rb : kGsBatch;
