@@ -562,8 +562,8 @@ int launch_geometry(const stem_det& det, double r2, RowRun* rows, double2* kc, h
 // STEM_EOVERFLOW (the stored value is then not meaningful).
 //
 // FR = 128 writes whole 128-byte lines of D.  Where its counters do not hold all kept pixels, every chunk
-// of pixels would read and look up the block's events again: FR = 64 and 32 hold 351 and 800 pixels at
-// once (launch_bin's rule).
+// of pixels reads and looks up the block's events again: FR = 64 and 32 hold 351 and 800 pixels at
+// once (bin_frames).
 
 constexpr int kBinThreads = 256;
 constexpr int kBinWin = 6144;       // events per window of the frame map (a block of 128 frames at 40
@@ -990,6 +990,34 @@ static bool make_box(const stem_det& det, double r2, BinBox& box) {
   return cells > 0 && cells <= kBinBoxMax && box.bh <= kBoxRows && det.W < 65536 && det.H < 65536;
 }
 
+// Frames per workgroup for n_k pixels.  A workgroup costs 8 to 10 us before its events count (tables, map, the
+// chain of loads and LDS phases): where there are more of them than the GPU holds, 64 and 32 frames take 1.5 and 3
+// times as long a chunk of pixels as 128.  They gain where they take fewer chunks (every chunk looks every event up
+// again), the more events a frame the more (past 48 a workgroup of 128 frames takes a second window of kBinWin),
+// or where the GPU is not full.  The host does not know the events a frame, so the lines lie where the smaller
+// workgroup is not slower at 10 to 45 of them either.  One MI355X, 576 x 576 detector, us with FR = 128 / 64 / 32 at
+// 10 events a frame, then at 100 (1024 x 1024: at 45):
+//  - to 181 pixels, one chunk with any FR: 176 pixels, 1024 x 1024 frames 77 / 124 / 255, 102 / 155 / 299.
+//  - to 351, one chunk from 64 down: 345 pixels, 512 x 512 frames 46 / 45 / 79, 128 / 84 / 89; 1024 x 1024 173 / 176 /
+//    310, 192 / 186 / 337.
+//  - to 800, one chunk of 32 against c of 128: up to 2^15 frames for c = 2, 2^16 for 3, 2^18 for 4, any number for 5.
+//    370 pixels (3), 64 x 512 frames 18 / 19 / 21, 40 / 30 / 23; 512 x 512 60 / 74 / 79, 174 / 145 / 89.  707 (4), 512 x 512
+//    95 / 125 / 92, 265 / 244 / 131; 1024 x 1024 412 / 585 / 459, 436 / 590 / 467.  790 (5), 1024 x 1024 (10; 40 events)
+//    515 / 614 / 498, 577 / 660 / 519.
+//  - more, several chunks of any: 32 up to 2^13 frames, 64 up to 2^16.  900 pixels, 64 x 64 frames 20 / 21 / 20, 33 / 24 /
+//    19; 64 x 512 29 / 30 / 39, 67 / 50 / 40; 512 x 512 118 / 132 / 208, 332 / 259 / 223; 1024 x 1024 522 / 632 / 898, 563 /
+//    653 / 920.
+int bin_frames(int n_k, int64_t n_frames) {
+  constexpr int k128 = BinShape<128>::kKd, k64 = BinShape<64>::kKd, k32 = BinShape<32>::kKd;
+  if (n_k <= k128) return 128;
+  if (n_k <= k64) return 64;
+  if (n_k <= k32) {
+    const int c = (n_k + k128 - 1) / k128;
+    return c >= 5 || n_frames <= (c == 2 ? 1 << 15 : c == 3 ? 1 << 16 : 1 << 18) ? 32 : 128;
+  }
+  return n_frames <= 1 << 13 ? 32 : n_frames <= 1 << 16 ? 64 : 128;
+}
+
 bool bin_builds_sets(const stem_det& det, double r2) {
   BinBox box;
   return make_box(det, r2, box);
@@ -1012,18 +1040,10 @@ int launch_bin(const int32_t* idx, const int64_t* off, int64_t frame0, int64_t n
     const int64_t words = sj.cst ? (int64_t)sj.ncs * sj.nmw : 0;
     nset = (int)((1 + (sj.B >= 4 ? words : (words + kBinThreads / 64 - 1) / (kBinThreads / 64)) + 7) & ~7ll);
   }
-  // Frames per workgroup: 128; less where that takes fewer chunks of pixels.  Measured (one MI355X, 576 x 576
-  // detector, FR = 128 / 64 / 32): 256 x 256 scan, 707 pixels, 77 / 71 / 37 us; 512 x 512, 314 pixels, 95 / 56
-  // / 93 us; 1024 x 1024, 176 pixels (one chunk with any), 106 / 167 / 319 us.
-  auto chunks_of = [&](int fr) {
-    const int kd = fr == 128 ? BinShape<128>::kKd : fr == 64 ? BinShape<64>::kKd : BinShape<32>::kKd;
-    return (n_k + kd - 1) / kd;
-  };
-  auto blocks_of = [&](int fr) { return (n_frames + fr - 1) / fr; };
-  int fr = 128;
-  while (fr > 32 && chunks_of(fr / 2) < chunks_of(fr)) fr /= 2;
-  const int64_t fblocks = blocks_of(fr);
-  const dim3 grid((unsigned)(nset + fblocks * chunks_of(fr)));
+  const int fr = bin_frames(n_k, n_frames);
+  const int kd = fr == 128 ? BinShape<128>::kKd : fr == 64 ? BinShape<64>::kKd : BinShape<32>::kKd;
+  const int64_t fblocks = (n_frames + fr - 1) / fr;
+  const dim3 grid((unsigned)(nset + fblocks * ((n_k + kd - 1) / kd)));
   // BOX: the binning kernel's first workgroup writes the row runs and bin centres; otherwise the
   // per-pixel table needs them first
   GeomOut geo{};

@@ -21,6 +21,8 @@ struct ComOut {
   int64_t nplane;
   int32_t cx, cy;
 };
+// frames per workgroup of the binning (128, 64 or 32)
+int bin_frames(int n_k, int64_t n_frames);
 // binning; also writes the kept-set geometry (row runs, bin centres Kc), and builds the per-pixel
 // table lut[W*H] first when the kept bins' box is too large for LDS.  With com, the same pass also
 // writes the frames' centre of mass (as launch_com does).
