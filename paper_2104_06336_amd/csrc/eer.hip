@@ -319,9 +319,8 @@ __global__ void __launch_bounds__(kComThreads) k_annular(const int32_t* __restri
 // then adds the box to the global sum once.
 //
 // Bound by those global atomics: every workgroup adds the whole disk.  So one large workgroup per compute unit
-// (256 of 1024 threads), two counters per 64-bit atomic where the sum is aligned for it (a counter stays
-// below 2^32), and every workgroup starts its box at another place, so that they do not queue at the
-// same lines.  Measured at 4.2e7 events in 2^20 frames (4% outside the disk): 165 us with 512 workgroups of
+// (256 of 1024 threads), two counters per 64-bit atomic where the sum is aligned for it, and
+// every workgroup starts its box at another place, so that they do not queue at the same lines.  Measured at 4.2e7 events in 2^20 frames (4% outside the disk): 165 us with 512 workgroups of
 // 256 threads, 32-bit atomics and one order, 103 us now.
 
 constexpr int kSumBox = 128;
@@ -403,8 +402,13 @@ __global__ void __launch_bounds__(kSumThreads) k_sum_events(const int32_t* __res
     const int p = P * (i + start < n ? i + start : i + start - n);
     uint32_t* dst = sum + (int64_t)(by0 + p / bw) * div.mg.d + bx0 + p % bw;
     if constexpr (PAIR) {
+      // a left sum that wraps carries one into its neighbour, which is taken back (waiting for the old values
+      // costs 0.8 us)
       const unsigned long long c = *(const unsigned long long*)&s_box[p];
-      if (c) atomicAdd((unsigned long long*)dst, c);
+      if (c) {
+        const unsigned long long was = atomicAdd((unsigned long long*)dst, c);
+        if ((uint32_t)was + (uint32_t)c < (uint32_t)c) atomicSub(dst + 1, 1u);
+      }
     } else {
       const uint32_t c = s_box[p];
       if (c) atomicAdd(dst, c);
