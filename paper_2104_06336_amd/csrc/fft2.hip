@@ -770,13 +770,14 @@ __device__ __forceinline__ float2 dpc_descend(float2 gx, float2 gy, double qx, d
                                               double lam2, int n_iter, bool live) {
   const double q2 = qx * qx + qy * qy;
   const double d = lam1 + q2 + lam2 * q2 * q2;
-  if (!live || d == 0.0) return make_float2(0.f, 0.f);
+  if (!live || d == 0.0 || n_iter <= 0) return make_float2(0.f, 0.f);
   const double md = mu / d, r = 1.0 - md * q2;
-  double s = 0.0;
-  for (int l = 0; l < n_iter; ++l) s = s * r + 1.0;
+  double s = 1.0;
+  for (int l = 1; l < n_iter; ++l) s = s * r + 1.0;
   s *= md;
-  return make_float2((float)(s * (qx * (double)gx.y + qy * (double)gy.y)),
-                     (float)(-s * (qx * (double)gx.x + qy * (double)gy.x)));
+  // a zero b stays at Phi = 0 in every step, also where the steps diverge and S is not finite
+  const double br = qx * (double)gx.y + qy * (double)gy.y, bi = -(qx * (double)gx.x + qy * (double)gy.x);
+  return make_float2(br == 0.0 ? 0.f : (float)(s * br), bi == 0.0 ? 0.f : (float)(s * bi));
 }
 
 // ---------------------------------------------------------------------------------------------
