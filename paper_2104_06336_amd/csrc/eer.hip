@@ -24,8 +24,9 @@ constexpr int kComFrames = 256;  // of the run-length re-coding: thread t takes 
 // ---------------------------------------------------------------------------------------------
 // validation
 
-// Events are only read inside [lo_bound, hi_bound), the range the caller guarantees to be
-// allocated; offsets outside it are reported, never followed.
+// Only events inside [lo_bound, hi_bound), the range the caller guarantees to be allocated, are looked at; offsets
+// outside it are reported, never followed.  They are loaded by whole 16-byte lines, each of which holds at least
+// one of them (so it lies in the array's pages; the other entries of a line are masked), four in flight per thread.
 __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ idx,
                                                   const int64_t* __restrict__ off, int64_t frame0,
                                                   int64_t n_frames, int64_t n_events, int exact_count,
@@ -41,10 +42,8 @@ __global__ void __launch_bounds__(256) k_validate(const int32_t* __restrict__ id
   for (int64_t f = tid; f < n_frames; f += nthr)
     if (off[frame0 + f + 1] < off[frame0 + f]) bits |= STEM_EOFFSETS;
   if (bounds_ok) {
-    // whole 16-byte lines that hold at least one of the events (the others of a line are masked), four in
-    // flight per thread
-    const int sh = (int)((((uintptr_t)(idx + e0)) & 15) >> 2);
-    const int64_t al = e0 - sh, ng = (e1 - al + 3) >> 2;
+    const Lines ln = lines_of((uintptr_t)idx, e0, e1);
+    const int64_t al = ln.first, ng = ln.n;
     for (int64_t g0 = tid; g0 < ng; g0 += 4 * nthr) {
       int4 v[4];
 #pragma unroll

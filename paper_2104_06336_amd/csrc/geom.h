@@ -75,6 +75,16 @@ __device__ __forceinline__ uint32_t pix_bin(uint32_t x, const PixDiv& p) {
   else return __umulhi(x, p.mbin);
 }
 
+// The whole 16-byte lines of an int32 array at address base that hold at least one of its entries [e0, e1):
+// n of them, the first starting at entry `first` (up to three before e0).  None for an empty range.
+struct Lines {
+  int64_t first, n;
+};
+__host__ __device__ __forceinline__ Lines lines_of(uintptr_t base, int64_t e0, int64_t e1) {
+  const int64_t first = e0 - (int64_t)(((base + 4 * (uintptr_t)e0) & 15) >> 2);
+  return Lines{first, e1 > e0 ? (e1 - first + 3) >> 2 : 0};
+}
+
 // Centre of bin index j along an axis, relative to the zero-frequency pixel c, in unbinned
 // pixels: b*j + (b-1)/2 - c.  Exact in double (multiples of 1/2 far below 2^53).
 __host__ __device__ __forceinline__ double bin_centre(int b, int j, int c) {
