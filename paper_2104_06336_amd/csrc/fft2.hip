@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(64 * W) k_row_fft(RowFftArgs a, int in_mode, i
   __syncthreads();
   float2* buf = s_buf + wave * kWaveStride;
   const int64_t ntiles = (a.nrows + TR - 1) / TR;
-  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM;
+  const bool transposed = out_mode == OUT_T_C64;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t r0 = tile * TR + wave * B;
     float2 v[16];
@@ -202,11 +202,7 @@ __global__ void __launch_bounds__(64 * W) k_row_fft(RowFftArgs a, int in_mode, i
         const int w = rl / B, b = rl % B;
         const int64_t r = tile * TR + rl;
         if (r < a.nrows) {
-          const float2 x = s_buf[w * kWaveStride + fft_pad(b * N + m)];
-          const int64_t e = (int64_t)m * a.out_stride + r;
-          if (out_mode == OUT_T_C64) a.out_c[e] = x;
-          else if (out_mode == OUT_T_RE) a.out_f[e] = x.x;
-          else a.out_f[e] = x.y;
+          a.out_c[(int64_t)m * a.out_stride + r] = s_buf[w * kWaveStride + fft_pad(b * N + m)];
         }
       }
       __syncthreads();
@@ -409,7 +405,7 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
   }
   gen_twiddles(tw, (double2*)buf, p);
   const int64_t nbatch = (a.nrows + rb - 1) / rb;
-  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM;
+  const bool transposed = out_mode == OUT_T_C64;
   const uint32_t mrb = rb == 1 ? 0u : (uint32_t)((0x100000000ull + rb - 1) / rb);
   for (int64_t bt = blockIdx.x; bt < nbatch; bt += gridDim.x) {
     const int64_t r0 = bt * rb;
@@ -503,9 +499,7 @@ __global__ void __launch_bounds__(kGenThreads) k_grow_fft(RowFftArgs a, GPlan p,
       if (out_mode == OUT_ROW_C64) a.out_c[r * n + m] = v;
       else if (out_mode == OUT_ROW_RE) a.out_f[r * n + m] = v.x;
       else if (out_mode == OUT_ROW_IM) a.out_f[r * n + m] = v.y;
-      else if (out_mode == OUT_T_C64) a.out_c[(int64_t)m * a.out_stride + r] = v;
-      else if (out_mode == OUT_T_RE) a.out_f[(int64_t)m * a.out_stride + r] = v.x;
-      else a.out_f[(int64_t)m * a.out_stride + r] = v.y;
+      else a.out_c[(int64_t)m * a.out_stride + r] = v;
     }
     __syncthreads();
   }

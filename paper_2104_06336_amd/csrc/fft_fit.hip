@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(kGenThreads) k_fit_fft(RowFftArgs a, GPlan p, 
   gen_twiddles(tw, n);
   __syncthreads();
   const int64_t nbatch = (a.nrows + rb - 1) / rb;
-  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_T_RE || out_mode == OUT_T_IM || out_mode == OUT_X;
+  const bool transposed = out_mode == OUT_T_C64 || out_mode == OUT_X;
   const int nh = n / 2 + 1;
   for (int64_t bt = blockIdx.x; bt < nbatch; bt += gridDim.x) {
     const int64_t r0 = bt * rb;
@@ -191,15 +191,9 @@ __global__ void __launch_bounds__(kGenThreads) k_fit_fft(RowFftArgs a, GPlan p, 
             x = cnt > 0 ? make_float2(x.x / (float)cnt, x.y / (float)cnt) : make_float2(0.f, 0.f);
           }
           if (a.sum_out) a.sum_out[el] = x;
-        } else if (in_mode == IN_HALF_C64) {
-          const float2* hr = a.in_c + r * nh;
-          x = 2 * i <= n ? hr[i] : cconj(hr[n - i]);
         } else if (in_mode == IN_F32_PAIR) {
           x.x = a.in_f0[el] * a.s0;
           x.y = a.in_f1 ? a.in_f1[el] * a.s1 : 0.f;
-        } else if (in_mode == IN_F64_PAIR) {
-          x.x = (float)(a.in_d0[el] * (double)a.s0);
-          x.y = a.in_d1 ? (float)(a.in_d1[el] * (double)a.s1) : 0.f;
         } else if (in_mode == IN_U8) {
           x.x = (float)((const uint8_t*)a.in_u)[el];
         } else {
@@ -218,11 +212,8 @@ __global__ void __launch_bounds__(kGenThreads) k_fit_fft(RowFftArgs a, GPlan p, 
       const float2 y = buf[rl * n + m];
       const float2 v = cmul(inv ? cconj(y) : y, a.osc);
       if (out_mode == OUT_ROW_C64) a.out_c[r * n + m] = v;
-      else if (out_mode == OUT_ROW_RE) a.out_f[r * n + m] = v.x;
       else if (out_mode == OUT_ROW_IM) a.out_f[r * n + m] = v.y;
       else if (out_mode == OUT_T_C64) a.out_c[(int64_t)m * a.out_stride + r] = v;
-      else if (out_mode == OUT_T_RE) a.out_f[(int64_t)m * a.out_stride + r] = v.x;
-      else if (out_mode == OUT_T_IM) a.out_f[(int64_t)m * a.out_stride + r] = v.y;
       else if (m < nh) {
         const int64_t kd = r / a.xrows, y_ = r % a.xrows;
         a.out_c[(kd * nh + m) * a.xrows + y_] = v;
@@ -236,6 +227,8 @@ __global__ void __launch_bounds__(kGenThreads) k_fit_fft(RowFftArgs a, GPlan p, 
 
 int launch_fit_row_fft(int n, bool inverse, RowIn in, RowOut out, const RowFftArgs& a, hipStream_t stream) {
   if (a.nrows <= 0) return STEM_OK;
+  // the modes a fit uses
+  if (in == IN_F64_PAIR || in == IN_HALF_C64 || out == OUT_ROW_RE) return STEM_EINVAL;
   if (fast_length(n) && in != IN_U8 && in != IN_U16 && out != OUT_X)
     return launch_row_fft(n, inverse, in, out, a, stream);
   STEM_TRACE(a.tag ? a.tag : "row_fft", stream);

@@ -37,7 +37,7 @@ bool bin_builds_sets(const stem_det& det, double r2);
 
 // ---- fft2.hip: batched row FFTs of length n (power of two, 32..1024) --------------------------
 enum RowIn { IN_C64 = 0, IN_C64_SUM = 1, IN_F32_PAIR = 2, IN_F64_PAIR = 3, IN_HALF_C64 = 4, IN_U8 = 5, IN_U16 = 6 };
-enum RowOut { OUT_T_C64 = 0, OUT_ROW_C64 = 1, OUT_ROW_RE = 2, OUT_ROW_IM = 3, OUT_T_RE = 4, OUT_T_IM = 5, OUT_X = 6 };
+enum RowOut { OUT_T_C64 = 0, OUT_ROW_C64 = 1, OUT_ROW_RE = 2, OUT_ROW_IM = 3, OUT_X = 4 };
 
 struct RowFftArgs {
   int64_t nrows;
@@ -57,7 +57,7 @@ struct RowFftArgs {
   const void* in_u;        // IN_U8 / IN_U16 (launch_fit_row_fft only): real row r at in_u + r*n
   float s0, s1;
   // outputs
-  float2* out_c;           // OUT_T_*: element (r, m) at out[m*out_stride + r]; OUT_ROW_*: out[r*n + m];
+  float2* out_c;           // OUT_T_C64: element (r, m) at out[m*out_stride + r]; OUT_ROW_*: out[r*n + m];
                            // OUT_X (launch_fit_row_fft only): m <= n/2 of row r = kd*xrows + y at
                            // out[(kd*(n/2+1) + m)*xrows + y]
   int32_t xrows;
