@@ -211,12 +211,17 @@ __global__ void __launch_bounds__(kGenThreads) k_fit_fft(RowFftArgs a, GPlan p, 
       if (r >= a.nrows) continue;
       const float2 y = buf[rl * n + m];
       const float2 v = cmul(inv ? cconj(y) : y, a.osc);
-      if (out_mode == OUT_ROW_C64) a.out_c[r * n + m] = v;
-      else if (out_mode == OUT_ROW_IM) a.out_f[r * n + m] = v.y;
-      else if (out_mode == OUT_T_C64) a.out_c[(int64_t)m * a.out_stride + r] = v;
-      else if (m < nh) {
-        const int64_t kd = r / a.xrows, y_ = r % a.xrows;
-        a.out_c[(kd * nh + m) * a.xrows + y_] = v;
+      // (the same as a chain of conditions compiles to a slower kernel: 720 x 360, 176 pixels, a fit's forward 1117
+      // instead of 1068 us)
+      switch (out_mode) {
+        case OUT_ROW_C64: a.out_c[r * n + m] = v; break;
+        case OUT_ROW_IM: a.out_f[r * n + m] = v.y; break;
+        case OUT_T_C64: a.out_c[(int64_t)m * a.out_stride + r] = v; break;
+        default:  // OUT_X
+          if (m < nh) {
+            const int64_t kd = r / a.xrows, y_ = r % a.xrows;
+            a.out_c[(kd * nh + m) * a.xrows + y_] = v;
+          }
       }
     }
     __syncthreads();
