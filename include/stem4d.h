@@ -220,7 +220,8 @@ int virtual_annular(const int32_t* d_idx, const int64_t* d_off, int64_t frame0, 
 
 /* Sum of the frames [frame0, frame0 + n_frames) (Table 1 "sum all frames"): the
  * position-averaged diffraction pattern (PACBED), or over frames in vacuum the average probe.
- *   d_sum[ky*W + kx] += number of events of those frames at pixel (kx, ky)   (uint32 [H][W])
+ *   d_sum[ky*W + kx] += number of events of those frames at pixel (kx, ky)   (uint32 [H][W],
+ *                       each pixel modulo 2^32 by itself)
  * The sum is accumulated (the caller zeroes d_sum once, so chunks can be added). If d_mean is
  * not NULL it then receives d_mean[k] = (float)((double)d_sum[k] / n_frames) (float [H][W]).
  * Only the events [off[frame0], off[frame0 + n_frames]) are read (offsets validated by
@@ -299,7 +300,9 @@ int ssb_reconstruct_com(const int32_t* d_idx, const int64_t* d_off, int64_t fram
 /* The forward of a fit: ssb_reconstruct in mode FINALIZE or REFOCUS on accumulated events, for an
  * ssb_backward that follows.  Same results to FP32 rounding; at scan lengths other than powers of two
  * in [32, 1024] it uses the adjoint's transforms, whose rounding the FP64 gradient dL/dc carries, so that a
- * fit's gradients do not depend on faster transforms of the other modes.  STEM_EINVAL for another mode. */
+ * fit's gradients do not depend on faster transforms of the other modes.  (An ssb_backward that follows a
+ * FINALIZE of ssb_reconstruct with STEM_G_STORE reads the values which that one's transforms stored: as
+ * accurate, other rounding.)  STEM_EINVAL for another mode. */
 int ssb_fit_forward(const stem_det* det, const stem_scan* scan, const stem_optics* optics, const stem_ssb* ssb,
                     int mode, const float* d_theta, void* state, size_t state_bytes, float* d_phase,
                     int32_t* d_status, void* stream);

@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
   // the group: a range of the pixels, or (workgroup sums) every ng-th active one
   const int kd_a = a.wgsum ? a.k0 : a.k0 + (int)((int64_t)(a.k1 - a.k0) * g / ng);
   const int kd_b = a.wgsum ? a.k1 : a.k0 + (int)((int64_t)(a.k1 - a.k0) * (g + 1) / ng);
-    const int stride = a.wgsum ? ng - 1 : 0;  // active pixels between two of the group's
+  const int stride = a.wgsum ? ng - 1 : 0;  // active pixels between two of the group's
   float2 accd[16], accm[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) accd[i] = accm[i] = make_float2(0.f, 0.f);
