@@ -103,8 +103,8 @@ def load_traffic(kernel, workload):
 
 # rocprofv3 kernel names of the kernels bench.py reports, by their trace name
 PROFILED = {
-    "stem::k_com": "com_moments",
-    "stem::k_bin<unsigned char, true, false>": "bin_densify",
+    "stem::k_com<true, 2>": "com_moments",
+    "stem::k_bin<unsigned char, true, false, 128, true>": "bin_densify",
     "stem::k_xstage<stem::XfFft<1024>, unsigned char>": "xstage_fft",
     "stem::k_yreduce<stem::XfFft<1024>, true, false>": "ssb_yreduce",
     "stem::k_psum_stream<false>": "ssb_reduce",
