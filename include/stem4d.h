@@ -112,7 +112,9 @@ enum { STEM_G_RECOMPUTE = 0, STEM_G_STORE = 1 };
  *  d_bits:      8 or 16, element width of the binned count cube (a larger count sets
  *               STEM_EOVERFLOW; it is never clamped silently).
  *  scratch_mib: STEM_G_RECOMPUTE: at most this many MiB of row-transformed columns are held at
- *               once (0: 64 MiB; at least one pixel's); ignored by STEM_G_STORE. */
+ *               once (0: 64 MiB; at least one pixel's).  STEM_G_STORE: ignored where both scan lengths are
+ *               powers of two in [32, 1024]; at others a FINALIZE takes the pixels in chunks of that size
+ *               (0: all at once; a fit 64 MiB). */
 typedef struct {
   int32_t precision;
   int32_t normalize;
