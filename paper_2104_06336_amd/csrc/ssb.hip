@@ -159,10 +159,18 @@ static size_t make_layout(const stem_det& det, const stem_scan& scan, const stem
   if (g > smallest) g = smallest;
   L->groups = g < 1 ? 1 : g;
   L->nwy = L->fast ? (int64_t)((L->ncs + 3) / 4) * 4 * L->groups : gsum_waves(scan.ny, scan.nx, L->groups);
-  // workgroup sums where the waves' own partials would be more than eight planes
+  // Workgroup sums where the waves' own partials would be more than eight planes
   // (fewer workgroups, a whole number of rounds of the 512 the GPU holds, were no faster: aberrated sum at
-  // 512 x 512 131 us with 3 planes, 117 us with 5)
+  // 512 x 512 131 us with 3 planes, 117 us with 5).  But 257 column sets (10 planes) would make 771 workgroups, one and
+  // a half rounds, which costs more than a smaller sum of partials gives if the pixels come in one chunk.  Then
+  // the waves keep their own partials, or, with the values written, five planes are made of them: 1024 x 512,
+  // 314 pixels, finalize without / with phase factors, own partials 343 / 374 us, 3 planes 352 / 395, 5 planes 341 /
+  // 378 us; values written 255 / 379, 271 / 401 and 258 / 369 us (one MI355X).  Three planes stay where five leave a
+  // wave less than five pixels (79 pixels, values written 109 us with 5, 104 us with 3), and with few pixels on the
+  // matrix cores (BF16, 79 pixels: own partials 132, 3 planes 122 us; 176 pixels 220 and 227 us).
   L->wgroups = L->fast && L->groups > 8 ? (L->groups + 3) / 4 : 0;
+  if (L->wgroups && L->ncs > 256 && L->nchunks == 1)
+    L->wgroups = L->store ? (n_k >= 100 ? 5 : 3) : ssb.precision != STEM_FFT_FP32 && n_k < 140 ? 3 : 0;
   L->nww = (int64_t)L->ncs * 4 * L->wgroups;
   // the kernels over the stored values: a wave (refocus) or workgroup (adjoint) per column of the
   // whole plane and pixel group, about kPrunedBlocks of them, at most the fused kernels' partial
@@ -684,10 +692,11 @@ static int run_phase(const SsbLayout& L, const Bufs& b, const stem_scan& sc, int
   a.ready_val = ready_tag(L);
   // more than eight partials (on average, in segments) are added by a kernel of their own: the pass that
   // adds them itself took 24 us at 512 x 512 (10 segments) and 44 us at 256 x 256 (33 planes), but it is
-  // one launch less at 1024 x 1024 (5 planes, 4 segments)
+  // one launch less at 1024 x 1024 (5 planes, 4 segments).  From 2^18 frames on the pass has waves enough for ten
+  // planes: 1024 x 512 (10 planes) a finalize takes 343 us with them, 346 us with the kernel; 48 x 450 (9) 84 and 80 us
   RowIn in = IN_C64_SUM;
   int st;
-  if ((part_seg ? nwaves / nx : nparts) > 8) {
+  if ((part_seg ? nwaves / nx : nparts) > (!part_seg && L.F >= (1 << 18) ? 10 : 8)) {
     if ((st = launch_part_sum(ny, a, s))) return st;
     a.in_c = b.T;
     in = IN_C64;
