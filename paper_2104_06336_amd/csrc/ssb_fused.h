@@ -28,6 +28,7 @@ template <int N_>
 struct XfFft {
   static constexpr int N = N_;
   static constexpr bool kMfma = false;
+  static constexpr bool kFp16 = false;
   static constexpr int RL = fft_last_radix<N>();
   static constexpr int NB = N / RL;
   static constexpr bool kUniformCol = NB >= kWave;
@@ -53,6 +54,7 @@ template <int N_, int PREC>
 struct XfMfma {
   static constexpr int N = N_;
   static constexpr bool kMfma = true;
+  static constexpr bool kFp16 = PREC == STEM_DFT_FP16_SPLIT;
   static constexpr int slot_of(int) { return 0; }  // all 16 registers of a lane share its column
   static constexpr int kSlots = 1;
   static constexpr bool kUniformCol = false;        // (the lanes of a wave do not)
@@ -413,8 +415,10 @@ template <typename XF, bool CHI0, bool PWRITE>
 __global__ void __launch_bounds__(kYThreads, 2) k_yreduce(YArgs a, Optics o) {
   if (state_unready(a)) return;
   constexpr int NY = XF::N;
-  // with phase factors the matrix-core outputs change to the FFT's register layout (relay_layout)
-  constexpr bool kRelay = XF::kMfma && NY >= 64 && !CHI0;
+  // with phase factors the matrix-core outputs change to the FFT's register layout (relay_layout), but not where
+  // that spills more with the values written than it saves: 64 frequencies, and 256 in FP16 (256 x 1024, 314
+  // pixels 255 instead of 294 us, 707 pixels 496 instead of 591 us)
+  constexpr bool kRelay = XF::kMfma && NY >= 64 && !CHI0 && !(PWRITE && (NY == 64 || (NY == 256 && XF::kFp16)));
   using SL = std::conditional_t<kRelay, XfFft<NY>, XF>;
   __shared__ float2 s_tw[1024];
   __shared__ float2 s_buf[4 * kXWaveStride];
